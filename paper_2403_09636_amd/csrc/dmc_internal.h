@@ -92,7 +92,7 @@ struct PrefillParams {
   int64_t ks[3], vs[3], qs[3];
   const int32_t *prompt_lens;
   int32_t *slot_index;     // optional [U, n]
-  uint8_t *alpha;          // [U, max_prompt] (staged only for prompt attention / window)
+  uint8_t *alpha;          // [U, max_prompt] (staged for the passes that read them per token)
   float *omega;            // [U, max_prompt] (likewise)
   int32_t *count;          // [U, prompt_chunks] segment starts per 64-token chunk
   uint64_t *mask;          // [U, prompt_chunks] bit i: token 64 c + i starts a segment
@@ -103,6 +103,7 @@ struct PrefillParams {
   float c;
   int32_t n, units, hkv, hq, maxpages, log2p, omega_src, max_prompt, prompt_chunks,
       carry_blocks, decision_src;
+  int32_t item_tokens;     // prompt tokens per work item of the pages pass
 };
 
 // Floats per carry record: sum of omega * k (d), sum of omega * v (d), sum of

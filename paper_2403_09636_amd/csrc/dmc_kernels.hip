@@ -1283,21 +1283,6 @@ __device__ __forceinline__ int xcd_order(int lin, int n) {
   return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
 }
 
-// Importance omega of token t of unit (b, dg) (Sec. 3.1: sigmoid of the first
-// query neuron), per the configured source; floored at 2^-100.
-template <int ES>
-__device__ __forceinline__ float token_omega(const PrefillParams &p, int b, int t, int dg, int G) {
-  if (p.omega_src == 0)
-    return sigmoid_floor(load_elem<ES>(p.q, b * p.qs[0] + t * p.qs[1] + (dg * G) * p.qs[2]));
-  if (p.omega_src == 1) {
-    float sum = 0.0f;
-    for (int h = 0; h < G; ++h)
-      sum += sigmoid_floor(load_elem<ES>(p.q, b * p.qs[0] + t * p.qs[1] + (dg * G + h) * p.qs[2]));
-    return fmaxf(sum / G, 0x1p-100f);
-  }
-  return 1.0f;   // uniform weighting
-}
-
 // Pass 1, one workgroup per unit (units in XCD order): decisions from the
 // decision neuron k[0] (the first token always opens a slot), and per 64-token
 // chunk the mask and count of segment starts; the unit length.  STAGE (prompt
@@ -1344,6 +1329,16 @@ __global__ __launch_bounds__(kThreads) void prefill_decide_kernel(PrefillParams 
       k0[j] = neuron(kb, kst, koff, tw);
       q0[j] = STAGE && p.omega_src == 0 ? neuron(qb, qst, qoff, tw) : 0.0f;
     }
+    if (STAGE && p.omega_src == 1) {   // the group's sum, a batch of loads in flight per head
+      for (int h = 0; h < G; ++h) {
+        float x[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+          x[j] = neuron(qb + h * p.qs[2] * ES, qst, qoff, t00 + j * kThreads + wave * 64);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) q0[j] += sigmoid_floor(x[j]);
+      }
+    }
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int t0 = t00 + j * kThreads;
@@ -1354,7 +1349,9 @@ __global__ __launch_bounds__(kThreads) void prefill_decide_kernel(PrefillParams 
         const bool valid = t < nb;
         const int a = (t > 0 && k0[j] > p.c) ? 1 : 0;
         if (STAGE) {
-          const float om = p.omega_src == 0 ? sigmoid_floor(q0[j]) : token_omega<ES>(p, b, t, dg, G);
+          const float om = p.omega_src == 0 ? sigmoid_floor(q0[j])
+                           : p.omega_src == 1 ? fmaxf(q0[j] / G, 0x1p-100f)
+                                              : 1.0f;   // uniform weighting
           p.alpha[int64_t(u) * p.max_prompt + t] = valid ? a : 1;
           p.omega[int64_t(u) * p.max_prompt + t] = om;
         }
@@ -1543,25 +1540,36 @@ __device__ __forceinline__ int start_token(const uint64_t *masks, int chunks, in
   return none;
 }
 
-// Pass 3 (exact Algorithm 1), slot-aligned work items of about kItemTokens
-// prompt tokens.  Unit u of length l is cut into items of S_u slots, S_u =
-// l kItemTokens / n rounded up to a multiple of 32 (so an item of a highly
-// compressed head spans few slots and one of an uncompressed head many, and
-// every item reads about the same number of prompt rows).  32-slot alignment
-// keeps every 32-slot page -- the transposed value pages of grouped-query
-// caches included -- inside one item, written by one wave in whole rows, and
-// no later pass touches it.  The item's tokens run from the start of its first
+// Pass 3 (exact Algorithm 1), work items of about T = p.item_tokens prompt
+// tokens, one wave each.  An item of a unit of length l is a run of S_u = ceil(l T / n) slots
+// (an item of a highly compressed head spans few slots and one of an
+// uncompressed head many, so every item reads about the same number of prompt
+// rows).  Transposed value pages of grouped-query caches must leave one
+// workgroup in whole rows: their items are rounded up to whole 32-slot pages,
+// staged and written by the item's wave -- or, on layers that do not fill the
+// chip, where S_u is at most half a page (whose 32 slots would be many times T
+// tokens), to 8 or 16 slots, and the workgroup's four waves stage one or two
+// pages together and write them after a barrier.  No later pass touches a page.
+// The item's tokens run from the start of its first
 // slot's segment to the start of the segment after its last slot (the prompt
 // end for the unit's last slot), located in the start masks of pass 1; each
 // token is read once, by the item holding its segment.  A slot is the
 // omega-weighted sum of its segment's keys (element 0 zeroed) and values over
 // their omega sum, in fp32 -- the running mean Algorithm 1 holds at the
-// segment's end; the unit's last segment gives z.  Omega comes from the first
-// query neuron here.  With carry records enabled, the running sums of a
+// segment's end; the unit's last segment gives z.  Omega comes from the staged
+// importances when the decide pass wrote them, else from the first query neuron
+// here.  With carry records enabled, the running sums of a
 // segment that crosses a 32-token boundary t (t not a segment start) are
-// stored as they stand before t, for the prompt-attention pass.  Waves map to
-// (item k, unit u) with k outermost, in plain launch order, so every XCD gets
-// a mix of all units and items.
+// stored as they stand before t, for the prompt-attention pass.  On layers
+// that fill the chip waves map to (item, unit) with the item outermost: the
+// rows of neighbouring heads, adjacent in memory, are read at about the same
+// time (a 70B GQA prompt, batch 32: 1 % faster than one unit per workgroup).  On
+// smaller layers a workgroup's four waves take consecutive items of one unit,
+// the units rotating, so every XCD gets a mix.
+//
+// What bounds it: HBM once enough waves are resident (4.6-5.2 TB/s of counted
+// traffic on the large layers), else one wave's chain of dependent batches
+// (about 4 us per 16 rows): T shrinks on small layers (prefill_item_tokens).
 //
 // WIN (window grouping, Sec. 3.3; caches with transposed value pages): a
 // slot is the omega-weighted mean of its segment's last min(w, length)
@@ -1571,36 +1579,72 @@ __device__ __forceinline__ int start_token(const uint64_t *masks, int chunks, in
 // token ring from that segment's last tokens.  Writing the transposed value
 // pages here replaces a separate page-transpose pass after the chunked
 // window pass (Llama-2 70B GQA layer, w = 12: 1.92 -> 1.66 ms per call).
-#ifndef DMC_PF_ITEM_TOKENS
-#define DMC_PF_ITEM_TOKENS 128
-#endif
-constexpr int kItemTokens = DMC_PF_ITEM_TOKENS;
+constexpr int kMaxItemTokens = 128;     // prompt tokens per item of a layer that fills the chip
+constexpr int64_t kItemWaves = 6144;    // waves resident at once (six per SIMD, 256 compute units)
 
-// Slots per work item of a unit with l slots from a prompt of n tokens.
-__device__ __forceinline__ int item_slots(int l, int n) {
-  const int64_t want = (int64_t(l) * kItemTokens + n - 1) / max(n, 1);
-  return static_cast<int>(max<int64_t>(32, (want + 31) & ~int64_t(31)));
+// Prompt tokens per work item: 128 while that gives every wave slot of the chip
+// an item, fewer on smaller layers, down to one batch.
+int prefill_item_tokens(int64_t units, int n) {
+  const int64_t want = (units * n + kItemWaves - 1) / kItemWaves;
+  const int64_t whole = (want + kPfRows - 1) / kPfRows * kPfRows;
+  return static_cast<int>(std::min<int64_t>(kMaxItemTokens, std::max<int64_t>(kPfRows, whole)));
 }
 
-template <int ES, int D, bool VT, bool WIN>
-__global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p, int items) {
+// STAGED: omega from the decide pass's staged importances.  FULL: a layer that
+// fills the chip (transposed value pages; row caches choose at run time).
+template <int ES, int D, bool VT, bool WIN, bool STAGED, bool FULL>
+__global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p) {
   constexpr int E = D / 64;         // elements per lane
   constexpr int RB = D * ES;        // bytes per row
   static_assert(!VT || ES == 2, "transposed value pages are bf16");
   static_assert(!WIN || VT, "row-layout caches with a window take prefill_window_kernel");
+  static_assert(!WIN || STAGED, "window grouping reads staged importances");
   __shared__ __align__(16) unsigned char s_vt[VT ? kWaves * 32 * RB : 16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gw = blockIdx.x * kWaves + wave;
-  const int k = gw / p.units;
-  if (k >= items) return;
-  const int u = gw - k * p.units, b = u / p.hkv, g = u - b * p.hkv;
+  // full layers: item k of unit u is wave k units + u; else a workgroup holds
+  // items 4 kg .. 4 kg + 3 of one unit
+  const bool full = FULL || (!VT && p.item_tokens >= kMaxItemTokens);
+  const int idx = full ? blockIdx.x * kWaves + wave : blockIdx.x;
+  const int kg = idx / p.units;
+  const int u = full ? idx - kg * p.units : (idx - kg * p.units + kg) % p.units;
+  const int b = u / p.hkv, g = u - b * p.hkv;
   const int l = p.len[u];
   const int P = 1 << p.log2p;
-  const int S = item_slots(l, p.n);
-  const int s_lo = k * S;
-  if (s_lo >= l) return;
+  int S = static_cast<int>((int64_t(l) * p.item_tokens + p.n - 1) / p.n);   // slots per item
+  const bool shared = VT && !full && S <= 16;   // the workgroup's waves share 32-slot pages
+  if constexpr (VT) S = shared ? (S > 8 ? 16 : 8) : (S + 31) & ~31;
+  const int s_wg = full ? kg * S : kg * kWaves * S;   // (first slot of the workgroup's group)
+  const int s_lo = full ? s_wg : s_wg + wave * S;
+  if (s_wg >= l || (s_lo >= l && !shared)) return;
   const int pb = p.page_base[u];
   if (pb < 0) return;
+  // Byte offset of element e of staging row r: rows of RB bytes, unpadded (32 KB per
+  // workgroup, so that five fit a compute unit), with the 4-byte word index XORed by
+  // 8 (r / 8 mod 4).  A row write (64 lanes, consecutive words) and a column gather
+  // (lanes over 16 elements x 4 row groups) then touch distinct banks.
+  auto stage_at = [&](int r, int e) {
+    const int byte = 2 * e;
+    return r * RB + ((((byte >> 2) ^ (8 * ((r >> 3) & 3))) << 2) | (byte & 3));
+  };
+  // The value page of grouped-query caches, staged as 32 rows in LDS, goes out
+  // as V^T: lane (dim, quarter) gathers 8 slots of one dim -- conflict-free
+  // thanks to the swizzle -- and stores them as one 16-byte piece.  The loop is
+  // not unrolled: unrolled, its 64 reads in flight took 21 more VGPRs.
+  auto write_vt_page = [&](const unsigned char *rows, char *vtp, int i0, int i1) {
+#pragma unroll 1
+    for (int i = i0; i < i1; ++i) {
+      const int pc = i * 64 + lane, dim = pc >> 2, qq = pc & 3;
+      uint32_t w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        w[j] = uint32_t(*reinterpret_cast<const uint16_t *>(rows + stage_at(8 * qq + 2 * j, dim))) |
+               (uint32_t(*reinterpret_cast<const uint16_t *>(rows + stage_at(8 * qq + 2 * j + 1, dim)))
+                << 16);
+      __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]},
+                                  reinterpret_cast<u32x4 *>(vtp + dim * 64 + qq * 16));
+    }
+  };
+  if (!shared || s_lo < l) {   // (a wave of a shared group without slots goes to its barrier)
   const int s_hi = min(s_lo + S, l);
   const int nb = prompt_len(p, b, false);
   const int G = p.hq / p.hkv, dg = p.decision_src ? 0 : g;
@@ -1637,43 +1681,14 @@ __global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p
   const int64_t kst = p.ks[1] * ES, vst = p.vs[1] * ES;
   const int kst32 = __builtin_amdgcn_readfirstlane(static_cast<int>(kst));
   const int vst32 = __builtin_amdgcn_readfirstlane(static_cast<int>(vst));
-  unsigned char *stage = s_vt + (VT ? wave * 32 * RB : 0);
-  // Byte offset of element e of staging row r: rows of RB bytes, unpadded (32 KB per
-  // workgroup, so that five fit a compute unit), with the 4-byte word index XORed by
-  // 8 (r / 8 mod 4).  A row write (64 lanes, consecutive words) and a column gather
-  // (lanes over 16 elements x 4 row groups) then touch distinct banks.
-  auto stage_at = [&](int r, int e) {
-    const int byte = 2 * e;
-    return r * RB + ((((byte >> 2) ^ (8 * ((r >> 3) & 3))) << 2) | (byte & 3));
-  };
+  // staging rows: of the slot's page (one wave), or of the workgroup's slots
+  unsigned char *stage = s_vt + (VT && !shared ? wave * 32 * RB : 0);
   int s = s_lo;
   int a_cur = t_lo;   // first token of slot s
   float ak[E], av[E], zs = 0.0f;
 #pragma unroll
   for (int e = 0; e < E; ++e) ak[e] = av[e] = 0.0f;
 
-  // The value page of grouped-query caches, staged as 32 rows in LDS, goes out
-  // as V^T: lane (dim, quarter) gathers 8 slots of one dim -- conflict-free
-  // thanks to the swizzle -- and stores them as one 16-byte piece.  The loop is
-  // not unrolled: unrolled, its 64 reads in flight took 21 more VGPRs.
-  auto write_vt_page = [&](char *vtp) {
-    if constexpr (VT) {
-      wave_lds_sync();
-#pragma unroll 1
-      for (int i = 0; i < D * 4 / 64; ++i) {
-        const int pc = i * 64 + lane, dim = pc >> 2, qq = pc & 3;
-        uint32_t w[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          w[j] = uint32_t(*reinterpret_cast<const uint16_t *>(stage + stage_at(8 * qq + 2 * j, dim))) |
-                 (uint32_t(*reinterpret_cast<const uint16_t *>(stage + stage_at(8 * qq + 2 * j + 1, dim)))
-                  << 16);
-        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]},
-                                    reinterpret_cast<u32x4 *>(vtp + dim * 64 + qq * 16));
-      }
-      wave_lds_sync();   // the staging rows are read before they are refilled
-    }
-  };
   auto flush = [&]() {   // slot s = sums / zs
     const float inv = 1.0f / zs;
     float kq[E], vq[E];
@@ -1686,8 +1701,12 @@ __global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p
     char *pg = p.pool + int64_t(pb + (s >> p.log2p)) * p.page_bytes;
     store_e_nt<ES, E>(pg + int64_t(row) * RB + lane * E * ES, kq);
     if constexpr (VT) {
-      store_e<ES, E>(reinterpret_cast<char *>(stage + stage_at(row, lane * E)), vq);
-      if (row == 31 || s == s_hi - 1) write_vt_page(pg + 32 * RB);
+      store_e<ES, E>(reinterpret_cast<char *>(stage + stage_at(shared ? s - s_wg : row, lane * E)), vq);
+      if (!shared && (row == 31 || s == s_hi - 1)) {
+        wave_lds_sync();
+        write_vt_page(stage, pg + 32 * RB, 0, D * 4 / 64);
+        wave_lds_sync();   // the staging rows are read before they are refilled
+      }
     } else {
       store_e_nt<ES, E>(pg + int64_t(P) * RB + int64_t(row) * RB + lane * E * ES, vq);
     }
@@ -1703,7 +1722,7 @@ __global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p
     unsigned long long m0, m1;
   };
   const int nbat = (t_hi - t_lo + kPfRows - 1) / kPfRows;
-  const bool lead_q0 = p.omega_src == 0;
+  const bool lead_q0 = !STAGED && p.omega_src == 0;
   auto issue = [&](int bi, Batch &bt) {
     const int t2 = t_lo + bi * kPfRows, cnt = min(kPfRows, t_hi - t2);
     uint32_t need = ~0u;   // rows the batch needs (bit j: token t2 + j)
@@ -1732,12 +1751,10 @@ __global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p
       bt.vr[j].load_nt(raw_rsrc(vb2, on), lane_off, jj * vst32);
     }
     bt.q0 = 0;
-    if constexpr (WIN) {
-      // staged importances of the needed tokens (0 for the others)
-      if (lane < cnt && ((need >> lane) & 1u))
-        bt.q0 = __float_as_uint(p.omega[int64_t(u) * p.max_prompt + t2 + lane]);
-      return;
-    }
+    // staged importances (window grouping: of the needed tokens, 0 for the others)
+    if (STAGED && lane < cnt && (!WIN || ((need >> lane) & 1u)))
+      bt.q0 = __float_as_uint(p.omega[int64_t(u) * p.max_prompt + t2 + lane]);
+    if constexpr (WIN) return;
     if (lead_q0 && lane < cnt) {
       const int64_t qi = b * p.qs[0] + int64_t(t2 + lane) * p.qs[1] + (dg * G) * p.qs[2];
       bt.q0 = ES == 2 ? uint32_t(static_cast<const uint16_t *>(p.q)[qi]) << 16
@@ -1757,9 +1774,9 @@ __global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p
     uint32_t sb = static_cast<uint32_t>(w) & (kPfRows == 32 ? ~0u : ((1u << kPfRows) - 1u));
     if (t2 == t_lo) sb &= ~1u;
     const float om_lane = lane >= cnt ? 0.0f
-                          : WIN     ? __uint_as_float(bt.q0)
+                          : STAGED  ? __uint_as_float(bt.q0)
                           : lead_q0 ? sigmoid_floor(__uint_as_float(bt.q0))
-                                    : token_omega<ES>(p, b, t2 + lane, dg, G);
+                                    : 1.0f;   // uniform weighting
     if (p.slot_index && lane < cnt)
       p.slot_index[int64_t(u) * p.n + t2 + lane] = s + __popc(sb & ((2u << lane) - 1u));
 #pragma unroll
@@ -1848,6 +1865,17 @@ __global__ __launch_bounds__(kThreads) void prefill_pages_kernel(PrefillParams p
         }
       }
       if (lane == 0) p.win.seg_len[u] = len;
+    }
+  }
+  }
+  if constexpr (VT) {
+    if (shared) {   // the group's pages, a quarter of each per wave
+      constexpr int Q = D * 4 / 64 / kWaves;
+      __syncthreads();
+      for (int j = 0; j < S / 8 && s_wg + 32 * j < l; ++j)
+        write_vt_page(s_vt + j * 32 * RB,
+                      p.pool + int64_t(pb + (s_wg >> 5) + j) * p.page_bytes + 32 * RB, wave * Q,
+                      (wave + 1) * Q);
     }
   }
 }
@@ -2197,10 +2225,13 @@ hipError_t decode_by_group(int group, const DecodeParams &p, int grid, bool vt, 
 }
 
 template <int ES, int D>
-hipError_t prefill_impl(const PrefillParams &p, bool vt, hipStream_t s) {
+hipError_t prefill_impl(const PrefillParams &p0, bool vt, hipStream_t s) {
+  PrefillParams p = p0;
+  p.item_tokens = prefill_item_tokens(p.units, p.n);
   // decisions and importances are staged for the passes that read them per
-  // token: prompt attention (carry records enabled) and window grouping
-  const bool stage = p.carry != nullptr || p.win.window > 0;
+  // token -- prompt attention (carry records enabled) and window grouping -- and
+  // where an importance is a mean over the group's heads, formed once per token
+  const bool stage = p.carry != nullptr || p.win.window > 0 || p.omega_src == 1;
   // the neuron lines (one 128-byte line per token and unit) are kept for the
   // pages pass while they fit about twice the 256 MiB last-level cache:
   // measured, a Llama-2-7B layer (268 MB of lines) gains 50 us in the pages
@@ -2227,19 +2258,31 @@ hipError_t prefill_impl(const PrefillParams &p, bool vt, hipStream_t s) {
                      p.log2p);
   e = hipGetLastError();
   if (e != hipSuccess || p.n == 0) return e;
-  // items of S_u >= l_u kItemTokens / n slots: at most ceil(n / kItemTokens)
-  // per unit, and at most ceil(n / 32) (S_u >= 32, l_u <= n)
-  const int items = std::min((p.n + kItemTokens - 1) / kItemTokens, (p.n + 31) / 32);
-  const int64_t waves = int64_t(p.units) * items;
-  const int blocks = static_cast<int>((waves + kWaves - 1) / kWaves);
+  // items of S_u >= l_u T / n slots: at most ceil(n / T) per unit (kg >= that
+  // many exit: s_lo >= l_u), in groups of kWaves per unit on layers that do not
+  // fill the chip
+  const int items = (p.n + p.item_tokens - 1) / p.item_tokens;
+  const int64_t blocks = p.item_tokens >= kMaxItemTokens
+                             ? (int64_t(p.units) * items + kWaves - 1) / kWaves
+                             : int64_t(p.units) * ((items + kWaves - 1) / kWaves);
+  if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
   const bool win = p.win.window > 0;
+  auto pages = [&](auto vt_c, auto win_c, auto staged_c) {
+    constexpr bool VT = decltype(vt_c)::value, WIN = decltype(win_c)::value,
+                   ST = decltype(staged_c)::value;
+    if (VT && p.item_tokens >= kMaxItemTokens)
+      hipLaunchKernelGGL((prefill_pages_kernel<ES, D, VT, WIN, ST, VT>), dim3(unsigned(blocks)),
+                         dim3(kThreads), 0, s, p);
+    else
+      hipLaunchKernelGGL((prefill_pages_kernel<ES, D, VT, WIN, ST, false>), dim3(unsigned(blocks)),
+                         dim3(kThreads), 0, s, p);
+  };
+  const std::true_type yes;
+  const std::false_type no;
   if constexpr (ES == 2) {
-    if (vt && win)
-      hipLaunchKernelGGL((prefill_pages_kernel<ES, D, true, true>), dim3(blocks), dim3(kThreads), 0, s,
-                         p, items);
-    else if (vt)
-      hipLaunchKernelGGL((prefill_pages_kernel<ES, D, true, false>), dim3(blocks), dim3(kThreads), 0, s,
-                         p, items);
+    if (vt && win) pages(yes, yes, yes);
+    else if (vt && stage) pages(yes, no, yes);
+    else if (vt) pages(yes, no, no);
     if (vt) return hipGetLastError();
   }
   // Row-layout caches with a window take the chunked window pass: on a
@@ -2249,9 +2292,10 @@ hipError_t prefill_impl(const PrefillParams &p, bool vt, hipStream_t s) {
     const int nch = (p.n + 63) / 64;
     hipLaunchKernelGGL((prefill_window_kernel<ES, D>), dim3((nch + kWaves - 1) / kWaves, p.units),
                        dim3(kThreads), 0, s, p);
+  } else if (stage) {
+    pages(no, no, yes);
   } else {
-    hipLaunchKernelGGL((prefill_pages_kernel<ES, D, false, false>), dim3(blocks), dim3(kThreads), 0, s,
-                       p, items);
+    pages(no, no, no);
   }
   return hipGetLastError();
 }
