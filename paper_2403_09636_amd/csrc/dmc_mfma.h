@@ -190,5 +190,169 @@ __device__ __forceinline__ float add_pair(uint32_t pair, float acc) {
                                          __builtin_bit_cast(bf16x2_t, 0x3f803f80u), acc, false);
 }
 
+// ---------------------------------------------------------------------------
+// fp32 on the matrix cores (v_mfma_f32_32x32x2_f32: lane l holds A[l % 32][l / 32],
+// B[l / 32][l % 32]; register r of the result is row 8 (r / 4) + 4 (l / 32) + r % 4,
+// column l % 32).  Each k-step contracts one index per half of the wave, and any
+// pairing of indices may form a step, so that
+//   - contractions over the head dim take "row" operands: 16-byte loads of a
+//     row, half hb holding elements 8 j + 4 hb .. + 4 (step 4 j + i: its i-th);
+//   - contractions over the 32 rows of a block take the previous product's
+//     result registers as B operand unchanged (step r: row 8 (r / 4) + 4 hb +
+//     r % 4) against "column" operands: lane i holds elements NT i .. + NT - 1
+//     of that row (NT = D / 32, one per 32-element tile of the result: result
+//     row m of tile t is element NT m + t).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+template <int D>
+struct F32 {
+  static constexpr int NJ = D / 8, NT = D / 32;
+  static constexpr int kCol = D + 4;   // floats per column of the LDS areas (bank spread)
+  // LDS floats of a workgroup: the merge area ([kWaves][32][kCol]), which holds
+  // the staged column operands before the merge
+  static constexpr int kArea = kWaves * 32 * kCol;
+  typedef float f4_t __attribute__((ext_vector_type(4)));
+  typedef float col_t __attribute__((ext_vector_type(NT)));
+
+  // Row of result register r.
+  __device__ static __forceinline__ int row(int r, int hb) { return 8 * (r >> 2) + 4 * hb + (r & 3); }
+
+  // Row operand of the row at `p`.
+  __device__ static __forceinline__ void load_row(f4_t (&f)[NJ], const float *p, int hb) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) f[j] = *reinterpret_cast<const f4_t *>(p + 8 * j + 4 * hb);
+  }
+  // The workgroup's 32 columns' rows (row_ptr(c), nullptr: zeros) into LDS
+  // ([32][kCol], shared by its waves: in registers they would take up to half
+  // the register file at d = 128); element 0 left out of the products on request.
+  template <typename Row>
+  __device__ static __forceinline__ void stage(float *area, Row &&row_ptr, bool zero_first) {
+    for (int i = threadIdx.x; i < 32 * D / 4; i += kThreads) {
+      const int c = i / (D / 4), e = i % (D / 4);
+      const float *src = row_ptr(c);
+      f4_t x = src ? *reinterpret_cast<const f4_t *>(src + 4 * e) : f4_t{};
+      if (zero_first && e == 0) x[0] = 0.0f;
+      *reinterpret_cast<f4_t *>(area + c * kCol + 4 * e) = x;
+    }
+  }
+  // This lane's slice of its column's staged row.
+  __device__ static __forceinline__ const float *staged(const float *area, int lane) {
+    return area + (lane & 31) * kCol + 4 * (lane >> 5);
+  }
+  // Products of 32 rows with the staged columns over the head dim, in chains of
+  // 16 elements added up (one chain over the whole head dim rounds about a
+  // quarter more than the sum trees of a vector reduction).
+  __device__ static __forceinline__ f32x16_t dots(const f4_t (&a)[NJ], const float *cols) {
+    int off = 0;
+    asm volatile("" : "+v"(off));   // keeps the reads here: hoisted out of a block loop they
+    cols += off;                    // would hold D / 2 registers per operand throughout it
+    f32x16_t s = f32x16_t{};
+    f4_t b[2][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[0][i] = *reinterpret_cast<const f4_t *>(cols + 8 * i);
+#pragma unroll
+    for (int j = 0; j < NJ; j += 4) {
+      if (j + 4 < NJ) {   // the next group's column operands
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[(j / 4 + 1) & 1][i] = *reinterpret_cast<const f4_t *>(cols + 8 * (j + 4 + i));
+      }
+      const f4_t(&bj)[4] = b[(j / 4) & 1];
+      f32x16_t x = f32x16_t{}, y = f32x16_t{};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        x = mfma_f32(a[j + i / 4][i % 4], bj[i / 4][i % 4], x);
+        y = mfma_f32(a[j + 2 + i / 4][i % 4], bj[2 + i / 4][i % 4], y);
+      }
+      s = j == 0 ? x + y : s + (x + y);
+      __builtin_amdgcn_sched_barrier(0);   // groups interleaved would take 32 registers each
+    }
+    return s;
+  }
+  // acc[t] += (rows' elements)^T w over the block's 32 rows, w in
+  // result-register layout.  The column operands are loaded kChunk registers' rows at a
+  // time (all at once at d = 64; at d = 128 they would not fit beside the
+  // row operands): Cols holds a chunk, loaded by load(c) ahead of its use.
+  // row_ptr(i): row i of the block.  masked: some columns may not see some
+  // rows (weight 0), and 0 times an infinity or NaN would reach them through
+  // the product: such elements are left out and reported, to be added to the
+  // columns that see them after the block loop (add_nonfinite).
+  static constexpr int kChunk = D == 64 ? 16 : 8;
+  __device__ static __forceinline__ bool finite(float x) { return __builtin_fabsf(x) <= 3.402823466e38f; }
+  struct Cols {
+    col_t v[kChunk];
+    template <typename Row>
+    __device__ __forceinline__ void load(Row &&row_ptr, int c, int lane) {
+#pragma unroll
+      for (int r = 0; r < kChunk; ++r)
+        v[r] = *reinterpret_cast<const col_t *>(row_ptr(row(c * kChunk + r, lane >> 5)) + NT * (lane & 31));
+    }
+  };
+  template <bool MASKED, typename Row>
+  __device__ static __forceinline__ bool add_rows(f32x16_t (&acc)[NT], Cols &cols, Row &&row_ptr,
+                                                  const float (&w)[16], int lane, bool masked = MASKED) {
+    bool left_out = false;
+#pragma unroll
+    for (int c = 0; c < 16 / kChunk; ++c) {
+      if (c > 0) cols.load(row_ptr, c, lane);
+      if (MASKED && masked) {
+#pragma unroll
+        for (int r = 0; r < kChunk; ++r)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            left_out |= !finite(cols.v[r][t]);
+            cols.v[r][t] = finite(cols.v[r][t]) ? cols.v[r][t] : 0.0f;
+          }
+      }
+#pragma unroll
+      for (int r = 0; r < kChunk; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = mfma_f32(cols.v[r][t], w[c * kChunk + r], acc[t]);
+    }
+    return left_out;
+  }
+  // Adds the infinities and NaN of a block's rows to the columns that see them
+  // (sees(i): this lane's column sees row i).
+  template <typename Row, typename Sees>
+  __device__ static __forceinline__ void add_nonfinite(f32x16_t (&acc)[NT], Row &&row_ptr, Sees &&sees,
+                                                       int lane) {
+#pragma unroll 1
+    for (int i = 0; i < 32; ++i) {
+      if (!sees(i)) continue;
+      const float *x = row_ptr(i);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const col_t e = *reinterpret_cast<const col_t *>(x + NT * row(r, lane >> 5));
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t][r] += finite(e[t]) ? 0.0f : e[t];
+      }
+    }
+  }
+  // This wave's accumulator to its part of the merge area ([kWaves][32][kCol]).
+  __device__ static __forceinline__ void put(float *area, int wave, int lane, const f32x16_t (&acc)[NT]) {
+    float *c = area + (wave * 32 + (lane & 31)) * kCol;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      col_t x;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) x[t] = acc[t][r];
+      *reinterpret_cast<col_t *>(c + NT * row(r, lane >> 5)) = x;
+    }
+  }
+  // The sum over the waves of elements 4 e .. + 4 of column c.
+  __device__ static __forceinline__ f4_t sum(const float *area, int c, int e) {
+    f4_t s = f4_t{};
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+      s += *reinterpret_cast<const f4_t *>(area + (w * 32 + c) * kCol + 4 * e);
+    return s;
+  }
+};
+
+// Four consecutive floats at any 4-byte alignment.
+__device__ __forceinline__ void load4(const float *p, float *f) { __builtin_memcpy(f, p, 16); }
+
 }  // namespace
 }  // namespace dmc

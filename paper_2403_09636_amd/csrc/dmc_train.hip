@@ -18,10 +18,10 @@
 // states' gradients are carried back to the tokens (the closed form above),
 // and the decision / importance neurons get theirs through alpha and omega.
 //
-// Vector-ALU kernels (lanes own head-dim elements, one wave per group of
-// rows) serve every dtype; bf16 attention runs on the matrix cores
-// (v_mfma_f32_32x32x16_bf16) in four kernels: forward, dq, dV~, and dK~ with
-// the mask gradient.
+// Attention runs on the matrix cores in both dtypes (v_mfma_f32_32x32x16_bf16,
+// v_mfma_f32_32x32x2_f32): forward, dq, and the states' gradients.  The states
+// and token passes are matrix products for bf16 and vector-ALU kernels (lanes
+// own head-dim elements) for fp32.
 #include <type_traits>
 
 #include "dmc_mfma.h"
@@ -102,9 +102,8 @@ __global__ __launch_bounds__(kThreads) void train_decide_kernel(TrainParams p) {
   if (t == p.n - 1) p.mask[i] = 0.0f;   // the last state has no successor
 }
 
-// Unrolled states, one wave per (unit, 64 positions), NP positions at a
-// time: state j is the closed-form partial accumulation over its window,
-// summed from token j down to the window start with the running product of
+// Unrolled states (fp32), one wave per (unit, NP positions): state j is the
+// closed-form partial accumulation over its window, summed from token j down to the window start with the running product of
 // alphas.  The NP positions share their tokens' rows, which are loaded in
 // batches and added to every position whose window holds them (each
 // position's sum runs over its tokens in the same descending order).
@@ -113,74 +112,72 @@ __global__ __launch_bounds__(64) void train_states_kernel(TrainParams p) {
   constexpr int E = D / 64, NP = 8, kB = 8;
   const int u = blockIdx.y, lane = threadIdx.x;
   const int b = u / p.hkv, g = u - b * p.hkv;
-  const int j0 = blockIdx.x * 64, j1 = min(j0 + 64, p.n);
+  const int jg = blockIdx.x * NP;                 // first position
   const float *al = p.alpha + int64_t(u) * p.n;
   const float *om = p.omega + int64_t(u) * p.n;
   const char *kb = static_cast<const char *>(p.k) + (row_k(p, b, 0, g, D) + lane * E) * ES;
   const char *vb = static_cast<const char *>(p.v) + (row_k(p, b, 0, g, D) + lane * E) * ES;
   const int64_t rs = int64_t(p.hkv) * D * ES;   // bytes between tokens
   const float sqrt_d = kLog2e / p.scale_log2;
-  for (int jg = j0; jg < j1; jg += NP) {
-    const int np = min(NP, j1 - jg);
-    const int jl = jg + np - 1;                   // last position of the group
-    const int lo = max(0, jg - p.window + 1);     // first token any of them needs
-    float sk[NP][E], sv[NP][E], zs[NP], P[NP];
+  const int np = min(NP, p.n - jg);
+  const int jl = jg + np - 1;                   // last position of the group
+  const int lo = max(0, jg - p.window + 1);     // first token any of them needs
+  float sk[NP][E], sv[NP][E], zs[NP], P[NP];
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      zs[i] = 0.0f;
-      P[i] = 1.0f;
+  for (int i = 0; i < NP; ++i) {
+    zs[i] = 0.0f;
+    P[i] = 1.0f;
 #pragma unroll
-      for (int e = 0; e < E; ++e) sk[i][e] = sv[i][e] = 0.0f;
+    for (int e = 0; e < E; ++e) sk[i][e] = sv[i][e] = 0.0f;
+  }
+  for (int t0 = jl; t0 >= lo; t0 -= kB) {
+    float kk[kB][E], vv[kB][E], wa[kB], wo[kB];
+#pragma unroll
+    for (int q = 0; q < kB; ++q) {
+      const int t = max(t0 - q, lo);
+      load_e<ES, E>(kb + t * rs, kk[q]);
+      load_e<ES, E>(vb + t * rs, vv[q]);
+      wa[q] = al[t];
+      wo[q] = om[t];
     }
-    for (int t0 = jl; t0 >= lo; t0 -= kB) {
-      float kk[kB][E], vv[kB][E], wa[kB], wo[kB];
 #pragma unroll
-      for (int q = 0; q < kB; ++q) {
-        const int t = max(t0 - q, lo);
-        load_e<ES, E>(kb + t * rs, kk[q]);
-        load_e<ES, E>(vb + t * rs, vv[q]);
-        wa[q] = al[t];
-        wo[q] = om[t];
-      }
+    for (int q = 0; q < kB; ++q) {
+      const int t = t0 - q;
+      if (t < lo) break;
+      if (lane == 0) kk[q][0] = 0.0f;   // k_t[0] <- 0
 #pragma unroll
-      for (int q = 0; q < kB; ++q) {
-        const int t = t0 - q;
-        if (t < lo) break;
-        if (lane == 0) kk[q][0] = 0.0f;   // k_t[0] <- 0
+      for (int i = 0; i < NP; ++i) {
+        const int j = jg + i;
+        if (i >= np || t > j || t < j - p.window + 1) continue;
+        const float c = wo[q] * P[i];    // omega_t * prod_{r = t+1 .. j} alpha_r
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-          const int j = jg + i;
-          if (i >= np || t > j || t < j - p.window + 1) continue;
-          const float c = wo[q] * P[i];    // omega_t * prod_{r = t+1 .. j} alpha_r
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            sk[i][e] = fmaf(c, kk[q][e], sk[i][e]);
-            sv[i][e] = fmaf(c, vv[q][e], sv[i][e]);
-          }
-          zs[i] += c;
-          P[i] *= wa[q];
+        for (int e = 0; e < E; ++e) {
+          sk[i][e] = fmaf(c, kk[q][e], sk[i][e]);
+          sv[i][e] = fmaf(c, vv[q][e], sv[i][e]);
         }
+        zs[i] += c;
+        P[i] *= wa[q];
       }
     }
+  }
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      if (i >= np) break;
-      const int j = jg + i;
-      const float inv = 1.0f / zs[i];
+  for (int i = 0; i < NP; ++i) {
+    if (i >= np) break;
+    const int j = jg + i;
+    const float inv = 1.0f / zs[i];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        sk[i][e] *= inv;
-        sv[i][e] *= inv;
-      }
-      // Element 0 of a key state is never part of a score; it carries the
-      // state's mask entry times sqrt(d), which the matrix-core kernels add
-      // to the scores through a query element fixed at 1.
-      if (lane == 0) sk[i][0] = p.mask[int64_t(u) * p.n + j] * sqrt_d;
-      const int64_t o = (int64_t(u) * p.n + j) * D + lane * E;
-      store_e<ES, E>(static_cast<char *>(p.ks) + o * ES, sk[i]);
-      store_e<ES, E>(static_cast<char *>(p.vs) + o * ES, sv[i]);
-      if (lane == 0) p.z[int64_t(u) * p.n + j] = zs[i];
+    for (int e = 0; e < E; ++e) {
+      sk[i][e] *= inv;
+      sv[i][e] *= inv;
     }
+    // Element 0 of a key state is never part of a score; it carries the
+    // state's mask entry times sqrt(d), which the matrix-core kernels add
+    // to the scores through a query element fixed at 1.
+    if (lane == 0) sk[i][0] = p.mask[int64_t(u) * p.n + j] * sqrt_d;
+    const int64_t o = (int64_t(u) * p.n + j) * D + lane * E;
+    store_e<ES, E>(static_cast<char *>(p.ks) + o * ES, sk[i]);
+    store_e<ES, E>(static_cast<char *>(p.vs) + o * ES, sv[i]);
+    if (lane == 0) p.z[int64_t(u) * p.n + j] = zs[i];
   }
 }
 
@@ -318,248 +315,344 @@ __global__ __launch_bounds__(64) void train_states_mfma_kernel(TrainParams p) {
   }
 }
 
-// Rows handled by one wave of the attention kernels: TG tokens x G heads.
-template <int G>
-struct Rows {
-  static constexpr int TG = G >= 8 ? 1 : 8 / G;
-  static constexpr int R = TG * G;
-};
+// ---------------------------------------------------------------------------
+// fp32 attention, on v_mfma_f32_32x32x2_f32 (operand forms: F32).  One workgroup
+// = 32 columns of one unit -- query columns (token-major: column c is token
+// c / G, head c % G) in the forward and dq, states in the state-gradient kernel
+// -- whose four waves share the column operands and take every fourth 32-row
+// block of the other side, straight from global memory (the blocks are read
+// through L2, no LDS ring: a block's products take thousands of matrix cycles,
+// and each operand form is loaded one product ahead of its use).  The waves'
+// results meet in LDS at the end.  Splitting the rows over the waves of a
+// workgroup, rather than giving every wave its own columns, keeps the chip busy
+// at the sizes fp32 is used at (8 units of 640 tokens: 320 column tiles for 1024
+// SIMDs).  Bound by the fp32 matrix rate and by the longest column tile's chain
+// of blocks.  Forward + backward, 8 units of 640 tokens, d = 64, G = 2: 2970 ->
+// 170 us against one wave per 8 query rows (4 states) on the vector ALUs, whose
+// row sums took a cross-lane reduction per score; error against float64 0.5 of
+// it (row sums over a quarter of the blocks each).
+// ---------------------------------------------------------------------------
 
-// Forward attention over the states: one wave per (unit, TG tokens), row r =
-// token a + r / G, head r % G; online softmax in the log2 domain.
-template <int ES, int D, int G>
-__global__ __launch_bounds__(kThreads) void train_fwd_kernel(TrainParams p, int ngroups) {
-  constexpr int TG = Rows<G>::TG, R = Rows<G>::R, E = D / 64, kAhead = 4;
-  const int lane = threadIdx.x & 63;
-  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+// Forward: scores S[state][col], online softmax per wave, O^T[dim][col].
+template <int D, int G>
+__global__ __launch_bounds__(kThreads) void train_fwd_f32_kernel(TrainParams p, int ntiles) {
+  using F = F32<D>;
+  constexpr int T = 32 / G, NT = F::NT;
+  __shared__ __align__(16) float s_acc[F::kArea];
+  __shared__ float s_m[kWaves * 32], s_l[kWaves * 32];
   const int U = p.batch * p.hkv;
-  const int u = wid / ngroups;
-  if (u >= U) return;
-  const int a = (wid - u * ngroups) * TG;
-  const int cnt = min(TG, p.n - a);
+  const int u = blockIdx.x % U, tile = ntiles - 1 - static_cast<int>(blockIdx.x) / U;   // longest first
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, hb = lane >> 5;
   const int b = u / p.hkv, g = u - b * p.hkv;
-  float qr[R][E];
+  const int a = tile * T, tok = col / G, head = col - tok * G, t = a + tok;
+  const bool colv = t < p.n;
+  const int top = min(a + T, p.n);   // states 0 .. top - 1 feed this tile
+  const int nblk = (top + 31) >> 5;
+  const int64_t un = int64_t(u) * p.n;
+  const float *ks = static_cast<const float *>(p.ks) + un * D, *vs = static_cast<const float *>(p.vs) + un * D;
+
+  // Q rows (q[0] is not part of the score)
+  F::stage(s_acc, [&](int c) -> const float * {
+    return a + c / G < p.n ? static_cast<const float *>(p.q) + row_q(p, b, a + c / G, g * G + c % G, D) : nullptr;
+  }, true);
+  __syncthreads();
+  const float *qs = F::staged(s_acc, lane);
+  typename F::f4_t kr[F::NJ];
+  float m = -1e30f, ls = 0.0f;
+  f32x16_t acc[NT];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = r / G, h = r - j * G;
+  for (int i = 0; i < NT; ++i) acc[i] = f32x16_t{};
+  auto row_of = [&](int s) { return int64_t(min(s, p.n - 1)) * D; };
+  F::load_row(kr, ks + row_of(wave * 32 + col), hb);
+  bool left_out = false;
+  // LAST: the diagonal's block, the only one with states past some column's token.
+  auto block = [&](int kb, auto last_c) {
+    constexpr bool LAST = decltype(last_c)::value;
+    typename F::Cols vc;
+    float bias[16];
+    auto value_row = [&](int i) { return vs + row_of(kb * 32 + i); };
+    vc.load(value_row, 0, lane);
 #pragma unroll
-    for (int e = 0; e < E; ++e) qr[r][e] = 0.0f;
-    if (j < cnt)
-      load_e<ES, E>(static_cast<const char *>(p.q) + (row_q(p, b, a + j, g * G + h, D) + lane * E) * ES,
-                    qr[r]);
-    if (lane == 0) qr[r][0] = 0.0f;   // q[0] is not part of the score
-  }
-  float m[R], l[R], acc[R][E];
+    for (int c = 0; c < 4; ++c) load4(p.mask + un + kb * 32 + 8 * c + 4 * hb, bias + 4 * c);   // (past n: not used)
+    const f32x16_t sc = F::dots(kr, qs);
+    if (!LAST) F::load_row(kr, ks + row_of((kb + kWaves) * 32 + col), hb);
+    float x[16], mx = neg_inf();
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    m[r] = neg_inf();
-    l[r] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[r][e] = 0.0f;
-  }
-  const int last = a + cnt - 1;
-  const char *ksb = static_cast<const char *>(p.ks) + (int64_t(u) * p.n * D + lane * E) * ES;
-  const char *vsb = static_cast<const char *>(p.vs) + (int64_t(u) * p.n * D + lane * E) * ES;
-  const float *mk = p.mask + int64_t(u) * p.n;
-  for (int s0 = 0; s0 <= last; s0 += kAhead) {
-    float kk[kAhead][E], vv[kAhead][E], bias[kAhead];
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      const int s = min(s0 + i, last);
-      load_e<ES, E>(ksb + int64_t(s) * D * ES, kk[i]);
-      load_e<ES, E>(vsb + int64_t(s) * D * ES, vv[i]);
-      bias[i] = mk[s] * kLog2e;
+    for (int r = 0; r < 16; ++r) {
+      const int s = kb * 32 + F::row(r, hb);
+      x[r] = sc[r] * p.scale_log2 + (!LAST || s < t ? bias[r] * kLog2e : 0.0f);
+      if (LAST && s > t) x[r] = neg_inf();
+      mx = fmaxf(mx, x[r]);
     }
+    const float mn = fmaxf(m, max_halves(mx));
+    const float f = fast_exp2(m - mn);
+    m = mn;
+    ls *= f;
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      const int s = s0 + i;
-      if (s > last) break;
+    for (int i = 0; i < NT; ++i) acc[i] *= f;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int t = a + r / G;
-        if (r / G >= cnt || s > t) continue;
-        float d = 0.0f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) d = fmaf(qr[r][e], kk[i][e], d);
-        const float x = wsum(d) * p.scale_log2 + (s < t ? bias[i] : 0.0f);
-        const float mn = fmaxf(m[r], x);
-        const float f = fast_exp2(m[r] - mn), w = fast_exp2(x - mn);
-        l[r] = l[r] * f + w;
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[r][e] = fmaf(acc[r][e], f, w * vv[i][e]);
-        m[r] = mn;
-      }
+    for (int r = 0; r < 16; ++r) {
+      x[r] = fast_exp2(x[r] - mn);
+      ls += x[r];
     }
+    left_out |= F::template add_rows<LAST>(acc, vc, value_row, x, lane);
+  };
+#pragma unroll 1
+  for (int kb = wave; kb < nblk - 1; kb += kWaves) block(kb, std::false_type{});
+  if (((nblk - 1) & (kWaves - 1)) == wave) block(nblk - 1, std::true_type{});
+  if (__any(left_out))
+    F::add_nonfinite(acc, [&](int i) { return vs + row_of((a & ~31) + i); },
+                     [&](int i) { return (a & ~31) + i <= t; }, lane);
+  ls += __shfl_xor(ls, 32, 64);
+  if (hb == 0) {
+    s_m[wave * 32 + col] = m;
+    s_l[wave * 32 + col] = ls;
   }
+  __syncthreads();
+  float M = s_m[col], L = 0.0f;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = r / G, h = r - j * G;
-    if (j >= cnt) continue;
-    float o[E];
-    const float inv = 1.0f / l[r];
+  for (int w = 1; w < kWaves; ++w) M = fmaxf(M, s_m[w * 32 + col]);
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = acc[r][e] * inv;
-    store_e<ES, E>(static_cast<char *>(p.out) + (row_q(p, b, a + j, g * G + h, D) + lane * E) * ES, o);
-    if (lane == 0) p.lse[(int64_t(u) * p.n + a + j) * G + h] = m[r] + __log2f(l[r]);
+  for (int w = 0; w < kWaves; ++w) L += s_l[w * 32 + col] * fast_exp2(s_m[w * 32 + col] - M);
+  const float f = fast_exp2(m - M) / L;
+#pragma unroll
+  for (int i = 0; i < NT; ++i) acc[i] *= f;
+  F::put(s_acc, wave, lane, acc);   // (every wave is past its last use of the staged rows)
+  if (tid < 32 && colv) p.lse[(un + t) * G + head] = M + __log2f(L);
+  __syncthreads();
+  for (int i = tid; i < 32 * D / 4; i += kThreads) {
+    const int c = i / (D / 4), e = i % (D / 4), tc = a + c / G;
+    if (tc < p.n)
+      *reinterpret_cast<typename F::f4_t *>(static_cast<float *>(p.out) + row_q(p, b, tc, g * G + c % G, D) + 4 * e) =
+          F::sum(s_acc, c, e);
   }
 }
 
 // dq of every query row, and D = sum(dout * out) of the row for the state
-// kernel: one wave per (unit, TG tokens), keys streamed as in the forward.
-template <int ES, int D, int G>
-__global__ __launch_bounds__(kThreads) void train_dq_kernel(TrainParams p, int ngroups) {
-  constexpr int TG = Rows<G>::TG, R = Rows<G>::R, E = D / 64, kAhead = 4;
-  const int lane = threadIdx.x & 63;
-  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+// kernel: P from the forward's statistics, dP[state][col], dQ^T[dim][col].
+template <int D, int G>
+__global__ __launch_bounds__(kThreads) void train_dq_f32_kernel(TrainParams p, int ntiles) {
+  using F = F32<D>;
+  constexpr int T = 32 / G, NT = F::NT;
+  __shared__ __align__(16) float s_acc[F::kArea];
   const int U = p.batch * p.hkv;
-  const int u = wid / ngroups;
-  if (u >= U) return;
-  const int a = (wid - u * ngroups) * TG;
-  const int cnt = min(TG, p.n - a);
+  const int u = blockIdx.x % U, tile = ntiles - 1 - static_cast<int>(blockIdx.x) / U;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, hb = lane >> 5;
   const int b = u / p.hkv, g = u - b * p.hkv;
-  float qr[R][E], dor[R][E], Lr[R], Dr[R], dq[R][E];
+  const int a = tile * T, tok = col / G, head = col - tok * G, t = a + tok;
+  const bool colv = t < p.n;
+  const int top = min(a + T, p.n);
+  const int nblk = (top + 31) >> 5;
+  const int64_t un = int64_t(u) * p.n;
+  const float *ks = static_cast<const float *>(p.ks) + un * D, *vs = static_cast<const float *>(p.vs) + un * D;
+
+  auto col_row = [&](const void *base, int c) -> const float * {
+    return a + c / G < p.n ? static_cast<const float *>(base) + row_q(p, b, a + c / G, g * G + c % G, D) : nullptr;
+  };
+  F::stage(s_acc, [&](int c) { return col_row(p.q, c); }, true);
+  F::stage(s_acc + 32 * F::kCol, [&](int c) { return col_row(p.dout, c); }, false);
+  __syncthreads();
+  const float *qs = F::staged(s_acc, lane), *dos = F::staged(s_acc + 32 * F::kCol, lane);
+  typename F::f4_t kr[F::NJ], vr[F::NJ];
+  float Lc = 0.0f, Dc = 0.0f;
+  if (colv) {
+    F::load_row(kr, col_row(p.out, col), hb);
+    Lc = p.lse[(un + t) * G + head];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = r / G, h = r - j * G;
+    for (int j = 0; j < F::NJ; ++j) {
+      const typename F::f4_t d4 = *reinterpret_cast<const typename F::f4_t *>(dos + 8 * j);
+      float part = 0.0f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) qr[r][e] = dor[r][e] = dq[r][e] = 0.0f;
-    Lr[r] = 0.0f;
-    Dr[r] = 0.0f;
-    if (j < cnt) {
-      const int64_t ro = row_q(p, b, a + j, g * G + h, D) + lane * E;
-      float of[E];
-      load_e<ES, E>(static_cast<const char *>(p.q) + ro * ES, qr[r]);
-      load_e<ES, E>(static_cast<const char *>(p.dout) + ro * ES, dor[r]);
-      load_e<ES, E>(static_cast<const char *>(p.out) + ro * ES, of);
-      float d = 0.0f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) d = fmaf(dor[r][e], of[e], d);
-      Dr[r] = wsum(d);
-      Lr[r] = p.lse[(int64_t(u) * p.n + a + j) * G + h];
-      if (lane == 0) p.dsum[(int64_t(u) * p.n + a + j) * G + h] = Dr[r];
-    }
-    if (lane == 0) qr[r][0] = 0.0f;
-  }
-  const int last = a + cnt - 1;
-  const char *ksb = static_cast<const char *>(p.ks) + (int64_t(u) * p.n * D + lane * E) * ES;
-  const char *vsb = static_cast<const char *>(p.vs) + (int64_t(u) * p.n * D + lane * E) * ES;
-  const float *mk = p.mask + int64_t(u) * p.n;
-  for (int s0 = 0; s0 <= last; s0 += kAhead) {
-    float kk[kAhead][E], vv[kAhead][E], bias[kAhead];
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      const int s = min(s0 + i, last);
-      load_e<ES, E>(ksb + int64_t(s) * D * ES, kk[i]);
-      load_e<ES, E>(vsb + int64_t(s) * D * ES, vv[i]);
-      bias[i] = mk[s] * kLog2e;
-    }
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      const int s = s0 + i;
-      if (s > last) break;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int t = a + r / G;
-        if (r / G >= cnt || s > t) continue;
-        float d = 0.0f, dp = 0.0f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          d = fmaf(qr[r][e], kk[i][e], d);
-          dp = fmaf(dor[r][e], vv[i][e], dp);
-        }
-        const float x = wsum(d) * p.scale_log2 + (s < t ? bias[i] : 0.0f);
-        const float pr = fast_exp2(x - Lr[r]);
-        const float ds = pr * (wsum(dp) - Dr[r]);
-#pragma unroll
-        for (int e = 0; e < E; ++e) dq[r][e] = fmaf(ds, kk[i][e], dq[r][e]);
-      }
+      for (int i = 0; i < 4; ++i) part = fmaf(d4[i], kr[j][i], part);
+      Dc += part;
     }
   }
-  const float sc = p.scale_log2 / kLog2e;   // 1 / sqrt(d)
+  Dc += __shfl_xor(Dc, 32, 64);
+  if (tid < 32 && colv) p.dsum[(un + t) * G + head] = Dc;
+
+  f32x16_t acc[NT];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = r / G, h = r - j * G;
-    if (j >= cnt) continue;
+  for (int i = 0; i < NT; ++i) acc[i] = f32x16_t{};
+  auto row_of = [&](int s) { return int64_t(min(s, p.n - 1)) * D; };
+  F::load_row(kr, ks + row_of(wave * 32 + col), hb);
+  bool left_out = false;
+  auto block = [&](int kb, auto last_c) {   // as in the forward
+    constexpr bool LAST = decltype(last_c)::value;
+    F::load_row(vr, vs + row_of(kb * 32 + col), hb);   // lands while the scores run
+    typename F::Cols kc;
+    float bias[16];
+    auto key_row = [&](int i) { return ks + row_of(kb * 32 + i); };
+    kc.load(key_row, 0, lane);
 #pragma unroll
-    for (int e = 0; e < E; ++e) dq[r][e] *= sc;
-    if (lane == 0) dq[r][0] = 0.0f;   // q[0] reaches the loss through omega only (added later)
-    store_e<ES, E>(static_cast<char *>(p.dq) + (row_q(p, b, a + j, g * G + h, D) + lane * E) * ES,
-                   dq[r]);
+    for (int c = 0; c < 4; ++c) load4(p.mask + un + kb * 32 + 8 * c + 4 * hb, bias + 4 * c);
+    const f32x16_t sc = F::dots(kr, qs);
+    const f32x16_t dp = F::dots(vr, dos);
+    if (!LAST) F::load_row(kr, ks + row_of((kb + kWaves) * 32 + col), hb);
+    float ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int s = kb * 32 + F::row(r, hb);
+      const float x = sc[r] * p.scale_log2 + (!LAST || s < t ? bias[r] * kLog2e : 0.0f);
+      ds[r] = LAST && s > t ? 0.0f : fast_exp2(x - Lc) * (dp[r] - Dc);
+    }
+    left_out |= F::template add_rows<LAST>(acc, kc, key_row, ds, lane);
+  };
+#pragma unroll 1
+  for (int kb = wave; kb < nblk - 1; kb += kWaves) block(kb, std::false_type{});
+  if (((nblk - 1) & (kWaves - 1)) == wave) block(nblk - 1, std::true_type{});
+  if (__any(left_out))
+    F::add_nonfinite(acc, [&](int i) { return ks + row_of((a & ~31) + i); },
+                     [&](int i) { return (a & ~31) + i <= t; }, lane);
+  const float sc_out = p.scale_log2 / kLog2e;   // 1 / sqrt(d)
+#pragma unroll
+  for (int i = 0; i < NT; ++i) acc[i] *= sc_out;
+  __syncthreads();   // the staged rows' last use
+  F::put(s_acc, wave, lane, acc);
+  __syncthreads();
+  for (int i = tid; i < 32 * D / 4; i += kThreads) {
+    const int c = i / (D / 4), e = i % (D / 4), tc = a + c / G;
+    if (tc < p.n) {
+      typename F::f4_t x = F::sum(s_acc, c, e);
+      if (e == 0) x[0] = 0.0f;   // q[0] reaches the loss through omega only (added later)
+      *reinterpret_cast<typename F::f4_t *>(static_cast<float *>(p.dq) + row_q(p, b, tc, g * G + c % G, D) + 4 * e) = x;
+    }
   }
 }
 
-// Gradients of the states and of the mask entries: one wave per (unit, KB
-// states), every query row (token >= state, all G heads) streamed.
-template <int ES, int D, int G>
-__global__ __launch_bounds__(kThreads) void train_dkv_kernel(TrainParams p, int nblocks) {
-  constexpr int E = D / 64, KB = 4;
-  const int lane = threadIdx.x & 63;
-  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+// Gradients of the states and of the mask entries: query rows r = t G + h
+// against 32 states, S[row][state] and dP[row][state], then dV~^T[dim][state]
+// and dK~^T[dim][state].  PART 0 computes both; at d = 128, where both sets of
+// operands exceed the register file, PART 1 is dV~ alone and PART 2 dK~ and the
+// mask gradient.
+template <int D, int G, int PART>
+__global__ __launch_bounds__(kThreads) void train_dkv_f32_kernel(TrainParams p, int ntiles) {
+  using F = F32<D>;
+  constexpr int NT = F::NT;
+  constexpr bool DV = PART != 2, DK = PART != 1;
+  __shared__ __align__(16) float s_acc[F::kArea];
+  __shared__ float s_dm[kWaves * 32];
   const int U = p.batch * p.hkv;
-  const int u = wid / nblocks;
-  if (u >= U) return;
-  const int j0 = (wid - u * nblocks) * KB;
-  const int kc = min(KB, p.n - j0);
+  const int u = blockIdx.x % U, tile = blockIdx.x / U;   // earliest states (most rows) first
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, hb = lane >> 5;
   const int b = u / p.hkv, g = u - b * p.hkv;
-  float kk[KB][E], vv[KB][E], bias[KB], dk[KB][E], dv[KB][E], dm[KB];
+  const int js = tile * 32 + col;   // this lane's state (column)
+  const bool sok = js < p.n;
+  const int64_t un = int64_t(u) * p.n;
+  const int nrows = p.n * G;
+  const int qb0 = tile * G, qb1 = (nrows + 31) >> 5;   // row blocks of tokens >= the first state
+
+  // K~ (element 0 carries the mask entry, not a key) and V~ rows of the states
+  auto state_row = [&](const void *base, int c) -> const float * {
+    return tile * 32 + c < p.n ? static_cast<const float *>(base) + (un + tile * 32 + c) * D : nullptr;
+  };
+  F::stage(s_acc, [&](int c) { return state_row(p.ks, c); }, true);
+  if constexpr (DK) F::stage(s_acc + 32 * F::kCol, [&](int c) { return state_row(p.vs, c); }, false);
+  __syncthreads();
+  const float *kst = F::staged(s_acc, lane), *vst = F::staged(s_acc + 32 * F::kCol, lane);
+  const float bias = sok ? p.mask[un + js] * kLog2e : 0.0f;
+  typename F::f4_t qr[F::NJ], dor[DK ? F::NJ : 1];
+
+  f32x16_t dk[DK ? NT : 1], dv[DV ? NT : 1];
+  if constexpr (DK) {
 #pragma unroll
-  for (int i = 0; i < KB; ++i) {
-    const int s = j0 + min(i, kc - 1);
-    const int64_t o = (int64_t(u) * p.n + s) * D + lane * E;
-    load_e<ES, E>(static_cast<const char *>(p.ks) + o * ES, kk[i]);
-    load_e<ES, E>(static_cast<const char *>(p.vs) + o * ES, vv[i]);
-    bias[i] = p.mask[int64_t(u) * p.n + s] * kLog2e;
-    dm[i] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) dk[i][e] = dv[i][e] = 0.0f;
+    for (int i = 0; i < NT; ++i) dk[i] = f32x16_t{};
   }
-  for (int t = j0; t < p.n; ++t) {
-    for (int h = 0; h < G; ++h) {
-      const int64_t ro = row_q(p, b, t, g * G + h, D) + lane * E;
-      float qf[E], df[E];
-      load_e<ES, E>(static_cast<const char *>(p.q) + ro * ES, qf);
-      load_e<ES, E>(static_cast<const char *>(p.dout) + ro * ES, df);
-      if (lane == 0) qf[0] = 0.0f;
-      const float L = p.lse[(int64_t(u) * p.n + t) * G + h];
-      const float Dt = p.dsum[(int64_t(u) * p.n + t) * G + h];
+  if constexpr (DV) {
 #pragma unroll
-      for (int i = 0; i < KB; ++i) {
-        const int s = j0 + i;
-        if (i >= kc || s > t) continue;
-        float d = 0.0f, dp = 0.0f;
+    for (int i = 0; i < NT; ++i) dv[i] = f32x16_t{};
+  }
+  float dm = 0.0f;
+  auto row_at = [&](int r) {
+    const int rc = min(r, nrows - 1);
+    return row_q(p, b, rc / G, g * G + rc % G, D);
+  };
+  auto load_q = [&](int qb) {
+    F::load_row(qr, static_cast<const float *>(p.q) + row_at(qb * 32 + col), hb);
+    if (hb == 0) qr[0][0] = 0.0f;   // q[0] is not part of the score
+  };
+  load_q(qb0 + wave);
+  bool out_v = false, out_k = false;
+#pragma unroll 1
+  for (int qb = qb0 + wave; qb < qb1; qb += kWaves) {
+    if constexpr (DK)   // lands while the scores run
+      F::load_row(dor, static_cast<const float *>(p.dout) + row_at(qb * 32 + col), hb);
+    typename F::Cols qc, oc;
+    float Lr[16], Dr[16];
+    auto q_row = [&](int i) { return static_cast<const float *>(p.q) + row_at(qb * 32 + i); };
+    auto do_row = [&](int i) { return static_cast<const float *>(p.dout) + row_at(qb * 32 + i); };
+    if constexpr (DV) oc.load(do_row, 0, lane);
+    if constexpr (DK) qc.load(q_row, 0, lane);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          d = fmaf(qf[e], kk[i][e], d);
-          dp = fmaf(df[e], vv[i][e], dp);
-        }
-        const float x = wsum(d) * p.scale_log2 + (s < t ? bias[i] : 0.0f);
-        const float pr = fast_exp2(x - L);
-        const float ds = pr * (wsum(dp) - Dt);
+    for (int c = 0; c < 4; ++c) {   // (the statistics are padded by 32 rows)
+      load4(p.lse + un * G + qb * 32 + 8 * c + 4 * hb, Lr + 4 * c);
+      if constexpr (DK) load4(p.dsum + un * G + qb * 32 + 8 * c + 4 * hb, Dr + 4 * c);
+    }
+    const f32x16_t sc = F::dots(qr, kst);
+    f32x16_t dp = f32x16_t{};
+    if constexpr (DK) dp = F::dots(dor, vst);
+    load_q(qb + kWaves);   // (past the last block: not used)
+    float pv[16], ds[16];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          dv[i][e] = fmaf(pr, df[e], dv[i][e]);
-          dk[i][e] = fmaf(ds, qf[e], dk[i][e]);
-        }
-        if (s < t) dm[i] += ds;
+    for (int r = 0; r < 16; ++r) {
+      const int rg = qb * 32 + F::row(r, hb), tq = rg / G;
+      const bool vis = rg < nrows && tq >= js;
+      const float x = sc[r] * p.scale_log2 + (tq > js ? bias : 0.0f);
+      pv[r] = vis ? fast_exp2(x - Lr[r]) : 0.0f;
+      if constexpr (DK) {
+        ds[r] = vis ? pv[r] * (dp[r] - Dr[r]) : 0.0f;
+        if (tq > js) dm += ds[r];
       }
     }
+    const bool masked = qb < qb0 + G;   // tokens before some column's state
+    if constexpr (DV) out_v |= F::template add_rows<true>(dv, oc, do_row, pv, lane, masked);
+    if constexpr (DK) out_k |= F::template add_rows<true>(dk, qc, q_row, ds, lane, masked);
   }
-  const float sc = p.scale_log2 / kLog2e;
-#pragma unroll
-  for (int i = 0; i < KB; ++i) {
-    if (i >= kc) break;
-    const int64_t o = (int64_t(u) * p.n + j0 + i) * D + lane * E;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      p.dks[o + e] = dk[i][e] * sc;
-      p.dvs[o + e] = dv[i][e];
+  if (__any(out_v || out_k)) {
+    for (int qb = qb0 + wave; qb < min(qb0 + G, qb1); qb += kWaves) {
+      auto sees = [&](int i) { return qb * 32 + i < nrows && (qb * 32 + i) / G >= js; };
+      if constexpr (DV)
+        F::add_nonfinite(dv, [&](int i) { return static_cast<const float *>(p.dout) + row_at(qb * 32 + i); },
+                         sees, lane);
+      if constexpr (DK)
+        F::add_nonfinite(dk, [&](int i) { return static_cast<const float *>(p.q) + row_at(qb * 32 + i); },
+                         sees, lane);
     }
-    if (lane == 0) p.dmask[int64_t(u) * p.n + j0 + i] = dm[i];
+  }
+  auto emit = [&](float *out, bool key) {   // the merged rows of the tile's states
+    __syncthreads();
+    for (int i = tid; i < 32 * D / 4; i += kThreads) {
+      const int c = i / (D / 4), e = i % (D / 4), j = tile * 32 + c;
+      if (j < p.n) {
+        typename F::f4_t x = F::sum(s_acc, c, e);
+        if (key && e == 0) x[0] = 0.0f;
+        *reinterpret_cast<typename F::f4_t *>(out + (un + j) * D + 4 * e) = x;
+      }
+    }
+  };
+  __syncthreads();   // the staged rows' last use
+  if constexpr (DV) {
+    F::put(s_acc, wave, lane, dv);
+    emit(p.dvs, false);
+    if constexpr (DK) __syncthreads();   // the merge area is reused
+  }
+  if constexpr (DK) {
+    const float sc_k = p.scale_log2 / kLog2e;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) dk[i] *= sc_k;
+    F::put(s_acc, wave, lane, dk);
+    dm += __shfl_xor(dm, 32, 64);
+    if (hb == 0) s_dm[wave * 32 + col] = dm;
+    emit(p.dks, true);
+    if (tid < 32 && sok) {
+      float x = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) x += s_dm[w * 32 + col];
+      p.dmask[un + js] = x;
+    }
   }
 }
 
-// States -> tokens, part 1, one wave per (unit, 64 tokens), NT tokens at a
-// time: token t feeds states j = t .. t + w - 1 with weight c_tj / z_j; its
+// States -> tokens, part 1 (fp32), one wave per (unit, NT tokens): token t feeds states j = t .. t + w - 1 with weight c_tj / z_j; its
 // key and value gradients gather those states' gradients, and e_tj = d loss /
 // d c_tj = ((k^_t - K~_j) . dK~_j + (v_t - V~_j) . dV~_j) / z_j is kept for
 // part 2.  The NT tokens share their states, which are loaded in batches;
@@ -571,81 +664,79 @@ __global__ __launch_bounds__(64) void train_tokens_kernel(TrainParams p) {
   constexpr int E = D / 64, NT = 8, kB = 4;
   const int u = blockIdx.y, lane = threadIdx.x;
   const int b = u / p.hkv, g = u - b * p.hkv;
-  const int t0 = blockIdx.x * 64, t1 = min(t0 + 64, p.n);
+  const int tg = blockIdx.x * NT;                 // first token
   const float *al = p.alpha + int64_t(u) * p.n;
   const float *om = p.omega + int64_t(u) * p.n;
   const float *zz = p.z + int64_t(u) * p.n;
   const int W = p.window;
-  for (int tg = t0; tg < t1; tg += NT) {
-    const int nt = min(NT, t1 - tg);
-    float kt[NT][E], vt[NT][E], dk[NT][E], dv[NT][E], P[NT], wt[NT], ereg[NT];
+  const int nt = min(NT, p.n - tg);
+  float kt[NT][E], vt[NT][E], dk[NT][E], dv[NT][E], P[NT], wt[NT], ereg[NT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      const int t = tg + min(i, nt - 1);
-      const int64_t ro = row_k(p, b, t, g, D) + lane * E;
-      load_e<ES, E>(static_cast<const char *>(p.k) + ro * ES, kt[i]);
-      load_e<ES, E>(static_cast<const char *>(p.v) + ro * ES, vt[i]);
-      if (lane == 0) kt[i][0] = 0.0f;
-      wt[i] = om[t];
-      P[i] = 1.0f;
-      ereg[i] = 0.0f;
+  for (int i = 0; i < NT; ++i) {
+    const int t = tg + min(i, nt - 1);
+    const int64_t ro = row_k(p, b, t, g, D) + lane * E;
+    load_e<ES, E>(static_cast<const char *>(p.k) + ro * ES, kt[i]);
+    load_e<ES, E>(static_cast<const char *>(p.v) + ro * ES, vt[i]);
+    if (lane == 0) kt[i][0] = 0.0f;
+    wt[i] = om[t];
+    P[i] = 1.0f;
+    ereg[i] = 0.0f;
 #pragma unroll
-      for (int e = 0; e < E; ++e) dk[i][e] = dv[i][e] = 0.0f;
+    for (int e = 0; e < E; ++e) dk[i][e] = dv[i][e] = 0.0f;
+  }
+  const int jl = min(tg + nt - 1 + W - 1, p.n - 1);   // last state any of them feeds
+  for (int jb = tg; jb <= jl; jb += kB) {
+    float dks[kB][E], dvs[kB][E], qs[kB], iz[kB], aj[kB];
+#pragma unroll
+    for (int q = 0; q < kB; ++q) {
+      const int j = min(jb + q, jl);
+      const int64_t so = (int64_t(u) * p.n + j) * D + lane * E;
+      float ks[E], vs[E];
+      load_e<ES, E>(static_cast<const char *>(p.ks) + so * ES, ks);
+      load_e<ES, E>(static_cast<const char *>(p.vs) + so * ES, vs);
+      qs[q] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        dks[q][e] = p.dks[so + e];
+        dvs[q][e] = p.dvs[so + e];
+        qs[q] = fmaf(ks[e], dks[q][e], qs[q]);   // this lane's part of K~ . dK~ + V~ . dV~
+        qs[q] = fmaf(vs[e], dvs[q][e], qs[q]);
+      }
+      iz[q] = 1.0f / zz[j];
+      aj[q] = al[j];
     }
-    const int jl = min(tg + nt - 1 + W - 1, p.n - 1);   // last state any of them feeds
-    for (int jb = tg; jb <= jl; jb += kB) {
-      float dks[kB][E], dvs[kB][E], qs[kB], iz[kB], aj[kB];
 #pragma unroll
-      for (int q = 0; q < kB; ++q) {
-        const int j = min(jb + q, jl);
-        const int64_t so = (int64_t(u) * p.n + j) * D + lane * E;
-        float ks[E], vs[E];
-        load_e<ES, E>(static_cast<const char *>(p.ks) + so * ES, ks);
-        load_e<ES, E>(static_cast<const char *>(p.vs) + so * ES, vs);
-        qs[q] = 0.0f;
+    for (int q = 0; q < kB; ++q) {
+      const int j = jb + q;
+      if (j > jl) break;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const int t = tg + i;
+        if (i >= nt || j < t || j > t + W - 1) continue;
+        if (j > t) P[i] *= aj[q];            // prod_{r = t+1 .. j} alpha_r
+        const float cz = wt[i] * P[i] * iz[q];
+        float ev = -qs[q];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          dks[q][e] = p.dks[so + e];
-          dvs[q][e] = p.dvs[so + e];
-          qs[q] = fmaf(ks[e], dks[q][e], qs[q]);   // this lane's part of K~ . dK~ + V~ . dV~
-          qs[q] = fmaf(vs[e], dvs[q][e], qs[q]);
+          dk[i][e] = fmaf(cz, dks[q][e], dk[i][e]);
+          dv[i][e] = fmaf(cz, dvs[q][e], dv[i][e]);
+          ev = fmaf(kt[i][e], dks[q][e], ev);
+          ev = fmaf(vt[i][e], dvs[q][e], ev);
         }
-        iz[q] = 1.0f / zz[j];
-        aj[q] = al[j];
-      }
-#pragma unroll
-      for (int q = 0; q < kB; ++q) {
-        const int j = jb + q;
-        if (j > jl) break;
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-          const int t = tg + i;
-          if (i >= nt || j < t || j > t + W - 1) continue;
-          if (j > t) P[i] *= aj[q];            // prod_{r = t+1 .. j} alpha_r
-          const float cz = wt[i] * P[i] * iz[q];
-          float ev = -qs[q];
-#pragma unroll
-          for (int e = 0; e < E; ++e) {
-            dk[i][e] = fmaf(cz, dks[q][e], dk[i][e]);
-            dv[i][e] = fmaf(cz, dvs[q][e], dv[i][e]);
-            ev = fmaf(kt[i][e], dks[q][e], ev);
-            ev = fmaf(vt[i][e], dvs[q][e], ev);
-          }
-          ev = wsum(ev) * iz[q];
-          if (lane == j - t) ereg[i] = ev;
-        }
+        ev = wsum(ev) * iz[q];
+        if (lane == j - t) ereg[i] = ev;
       }
     }
+  }
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      if (i >= nt) break;
-      const int t = tg + i;
-      if (lane < min(W, p.n - t)) p.e[(int64_t(u) * p.n + t) * W + lane] = ereg[i];
-      const int64_t ro = row_k(p, b, t, g, D) + lane * E;
-      if (lane == 0) dk[i][0] = 0.0f;   // element 0 gets the decision gradient in part 2
-      store_e<ES, E>(static_cast<char *>(p.dk) + ro * ES, dk[i]);
-      store_e<ES, E>(static_cast<char *>(p.dv) + ro * ES, dv[i]);
-    }
+  for (int i = 0; i < NT; ++i) {
+    if (i >= nt) break;
+    const int t = tg + i;
+    if (lane < min(W, p.n - t)) p.e[(int64_t(u) * p.n + t) * W + lane] = ereg[i];
+    const int64_t ro = row_k(p, b, t, g, D) + lane * E;
+    if (lane == 0) dk[i][0] = 0.0f;   // element 0 gets the decision gradient in part 2
+    store_e<ES, E>(static_cast<char *>(p.dk) + ro * ES, dk[i]);
+    store_e<ES, E>(static_cast<char *>(p.dv) + ro * ES, dv[i]);
   }
 }
 
@@ -1676,10 +1767,10 @@ hipError_t train_forward_impl(const TrainParams &p, hipStream_t s) {
     hipLaunchKernelGGL((train_qmajor_kernel<D, G, 0>), dim3(8 * ((U + 7) / 8) * ntiles),
                        dim3(kThreads), 0, s, p, ntiles);
   } else {
-    hipLaunchKernelGGL((train_states_kernel<ES, D>), dim3((p.n + 63) / 64, U), dim3(64), 0, s, p);
-    const int ngroups = (p.n + Rows<G>::TG - 1) / Rows<G>::TG;
-    hipLaunchKernelGGL((train_fwd_kernel<ES, D, G>), dim3(blocks_for(int64_t(U) * ngroups * 64)),
-                       dim3(kThreads), 0, s, p, ngroups);
+    hipLaunchKernelGGL((train_states_kernel<ES, D>), dim3((p.n + 7) / 8, U), dim3(64), 0, s, p);
+    const int ntiles = (p.n + 32 / G - 1) / (32 / G);
+    hipLaunchKernelGGL((train_fwd_f32_kernel<D, G>), dim3(unsigned(U) * ntiles), dim3(kThreads), 0, s, p,
+                       ntiles);
   }
   return hipGetLastError();
 }
@@ -1698,12 +1789,16 @@ hipError_t train_backward_impl(const TrainParams &p, hipStream_t s) {
     hipLaunchKernelGGL((train_dkv_mfma_kernel<D, G, 2>), dim3(8 * ((U + 7) / 8) * stiles),
                        dim3(kThreads), 0, s, p, stiles);
   } else {
-    const int ngroups = (p.n + Rows<G>::TG - 1) / Rows<G>::TG;
-    hipLaunchKernelGGL((train_dq_kernel<ES, D, G>), dim3(blocks_for(int64_t(U) * ngroups * 64)),
-                       dim3(kThreads), 0, s, p, ngroups);
-    const int nblocks = (p.n + 3) / 4;
-    hipLaunchKernelGGL((train_dkv_kernel<ES, D, G>), dim3(blocks_for(int64_t(U) * nblocks * 64)),
-                       dim3(kThreads), 0, s, p, nblocks);
+    const int ntiles = (p.n + 32 / G - 1) / (32 / G), stiles = (p.n + 31) / 32;
+    hipLaunchKernelGGL((train_dq_f32_kernel<D, G>), dim3(unsigned(U) * ntiles), dim3(kThreads), 0, s, p,
+                       ntiles);
+    const dim3 sgrid(unsigned(U) * stiles);
+    if constexpr (D == 64) {
+      hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 0>), sgrid, dim3(kThreads), 0, s, p, stiles);
+    } else {
+      hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 1>), sgrid, dim3(kThreads), 0, s, p, stiles);
+      hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 2>), sgrid, dim3(kThreads), 0, s, p, stiles);
+    }
   }
   if constexpr (ES == 2) {
     const dim3 grid((p.n + 31) / 32, U);
@@ -1715,7 +1810,7 @@ hipError_t train_backward_impl(const TrainParams &p, hipStream_t s) {
       default: hipLaunchKernelGGL((train_tokens_mfma_kernel<D, 6>), grid, dim3(64), 0, s, p); break;
     }
   } else {
-    hipLaunchKernelGGL((train_tokens_kernel<ES, D>), dim3((p.n + 63) / 64, U), dim3(64), 0, s, p);
+    hipLaunchKernelGGL((train_tokens_kernel<ES, D>), dim3((p.n + 7) / 8, U), dim3(64), 0, s, p);
   }
   hipLaunchKernelGGL((train_neurons_kernel<ES, D>), dim3(blocks_for(int64_t(U) * p.n)),
                      dim3(kThreads), 0, s, p);

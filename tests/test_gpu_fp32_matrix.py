@@ -1,0 +1,55 @@
+"""GPU: the fp32 matrix-core attention kernels at the edges of their 32-row
+blocks, against the oracles, and rows that are not finite (an infinity or NaN
+reaches only the outputs that read it)."""
+import numpy as np
+import pytest
+
+from tests.gpu_helpers import log
+from tests.test_gpu_train import test_train_forward_backward as check_train
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,G,B,Hkv,n,w", [
+    (64, 1, 1, 1, 31, 5), (64, 1, 1, 2, 32, 5), (128, 1, 1, 1, 33, 5),
+    (128, 8, 1, 1, 129, 12), (64, 4, 2, 1, 161, 31), (128, 2, 1, 1, 193, 12),
+])
+def test_train_blocks(torch_cuda, d, G, B, Hkv, n, w):
+    check_train(torch_cuda, ("fp32", d, G, B, Hkv, n, w, 5.0, 0.1, [3.0, 1.0][:Hkv], "lead", True))
+
+
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4)])
+def test_train_nonfinite_rows(torch_cuda, d, G):
+    import torch
+    import paper_2403_09636_amd as P
+    log(f"case nonfinite d={d} G={G}")
+    n, w, s, r = 77, 4, 40, 20
+    gen = torch.Generator().manual_seed(7 + d)
+    q, k, v, dout = (torch.randn((1, n, h, d), generator=gen).cuda() for h in (G, 1, 1, G))
+    noise = torch.zeros((1, n, 1), device="cuda")
+    tr = P.DMCTrainer(P.make_train_config(1, n, G, 1, d, "fp32", decision_bias=0.0, temperature=1.0,
+                                          window=w))
+
+    def run(v, dout):
+        out = tr.forward(q, k, v, noise)
+        return (out, *tr.backward(q, k, v, noise, out, dout))
+
+    ref = run(v, dout)
+    bad_v = v.clone()
+    bad_v[0, s, 0, 5] = float("inf")
+    out, dq, _, _ = run(bad_v, dout)
+    # queries before token s do not read it (rounding may differ: another path); dq[0] comes
+    # through omega from the states' gradients, which every later query feeds
+    for got, want in ((out, ref[0]), (dq[..., 1:], ref[1][..., 1:])):
+        assert torch.isfinite(got[0, :s]).all()
+        torch.testing.assert_close(got[0, :s], want[0, :s], rtol=1e-4, atol=1e-5)
+    assert not torch.isfinite(out[0, s]).all()
+    bad_do = dout.clone()
+    bad_do[0, r, 0, 3] = float("nan")
+    _, _, dk, dv = run(v, bad_do)
+    # states (and tokens) after row r do not feed it; dk[0] of token r + 1 holds state r's mask
+    # gradient, so the decision neuron is left out
+    for got, want in ((dk[..., 1:], ref[2][..., 1:]), (dv, ref[3])):
+        assert torch.isfinite(got[0, r + 1:]).all()
+        torch.testing.assert_close(got[0, r + 1:], want[0, r + 1:], rtol=1e-4, atol=1e-4)
+    assert torch.isnan(dv[0, r]).any()
