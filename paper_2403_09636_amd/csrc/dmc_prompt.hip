@@ -8,7 +8,7 @@
 // closed before it -- slots 0 .. seg(i)-1 of the compacted cache -- and the
 // running (partial) mean of its own segment up to and including token i.
 //
-// Both kernels run after the compaction passes, which leave in the
+// Both kernels (bf16, fp32) run after the compaction passes, which leave in the
 // workspace the decisions and importance scores of every prompt token, the
 // per-64-token segment-start counts, the finished cache and, for every
 // 32-token boundary that falls inside a segment, the segment's running sums
@@ -27,11 +27,6 @@
 
 namespace dmc {
 namespace {
-
-__device__ __forceinline__ float wave_sum(float x) {
-  x = row_sum<32>(x);
-  return x + __shfl_xor(x, 32, 64);
-}
 
 __device__ __forceinline__ int wave_sum_int(int x) {
 #pragma unroll
@@ -58,72 +53,12 @@ __device__ __forceinline__ int token_slots(const PromptParams &p, int u, int a, 
   return lane < cnt ? before + __popcll(mine & upto) - 1 : -1;
 }
 
-// Rebuilds the open-segment running sums of tokens [a, a + cnt) (cnt >= 1)
-// in token order, starting at the 32-token boundary at or below a: calls
-// snap(t, ak, av, zs) for every t >= a with the sums after token t, and
-// batch_end(t0) after each batch of 8 tokens t0 .. t0 + 7.  Lanes own
-// elements lane * E .. lane * E + E - 1; k[0] is read as 0.
-template <int ES, int D, typename Snap, typename BatchEnd>
-__device__ __forceinline__ void walk_open_state(const PromptParams &p, int u, int b, int g, int a,
-                                                int cnt, Snap &&snap, BatchEnd &&batch_end) {
-  constexpr int E = D / 64;
-  constexpr int kRows = 8;
-  const int lane = threadIdx.x & 63;
-  const int bs = a & ~31, end = a + cnt;
-  const uint8_t *al = p.alpha + int64_t(u) * p.max_prompt;
-  const float *om = p.omega + int64_t(u) * p.max_prompt;
-  float ak[E], av[E], zs = 0.0f;
-#pragma unroll
-  for (int e = 0; e < E; ++e) ak[e] = av[e] = 0.0f;
-  if (bs > 0 && al[bs] != 0) {   // the segment open at bs started earlier
-    const float *cr = p.carry + (int64_t(u) * p.carry_blocks + (bs >> 5)) * carry_stride(D);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      ak[e] = cr[lane * E + e];
-      av[e] = cr[D + lane * E + e];
-    }
-    zs = cr[2 * D];
-  }
-  const char *kbase = static_cast<const char *>(p.k) + (b * p.ks[0] + g * p.ks[2] + lane * E) * ES;
-  const char *vbase = static_cast<const char *>(p.v) + (b * p.vs[0] + g * p.vs[2] + lane * E) * ES;
-  const int64_t kst = p.ks[1] * ES, vst = p.vs[1] * ES;
-  for (int t0 = bs; t0 < end; t0 += kRows) {
-    float kk[kRows][E], vv[kRows][E], ww[kRows];
-    bool st[kRows];
-#pragma unroll
-    for (int j = 0; j < kRows; ++j) {
-      const int tj = min(t0 + j, end - 1);
-      load_e<ES, E>(kbase + tj * kst, kk[j]);
-      load_e<ES, E>(vbase + tj * vst, vv[j]);
-      ww[j] = om[tj];
-      st[j] = al[tj] == 0;
-    }
-#pragma unroll
-    for (int j = 0; j < kRows; ++j) {
-      const int tj = t0 + j;
-      if (tj < end) {
-        if (st[j]) {
-          zs = 0.0f;
-#pragma unroll
-          for (int e = 0; e < E; ++e) ak[e] = av[e] = 0.0f;
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const float kv = (lane * E + e == 0) ? 0.0f : kk[j][e];   // k_t[0] <- 0
-          ak[e] = fmaf(ww[j], kv, ak[e]);
-          av[e] = fmaf(ww[j], vv[j][e], av[e]);
-        }
-        zs += ww[j];
-        if (tj >= a) snap(tj, ak, av, zs);
-      }
-    }
-    batch_end(t0);
-  }
-}
-
 // Window grouping (Sec. 3.3): the open state of token t is the omega-
 // weighted mean of its segment's tokens max(segment start, t - w + 1) .. t.
-// Same interface as walk_open_state.  The walk starts at the 8-aligned token
+// Rebuilds it for tokens [a, a + cnt) (cnt >= 1) in token order: calls
+// snap(t, ak, av, zs) for every t >= a with the sums up to token t, and
+// batch_end(t0) after each batch of 8 tokens t0 .. t0 + 7.  Lanes own
+// elements lane * E .. lane * E + E - 1; k[0] is read as 0.  The walk starts at the 8-aligned token
 // at or below a - w + 1 with empty sums (no carry records: a window never
 // reaches further back), adds each token, restarts at segment starts and
 // removes the token that leaves the window (t - w, when it lies in the
@@ -801,122 +736,212 @@ __global__ __launch_bounds__(kThreads, 2) void prompt_mfma_kernel(PromptParams p
 }
 
 // ---------------------------------------------------------------------------
-// Vector-ALU kernel (every dtype; used for fp32).  One wave = one unit's
-// TG = max(1, 8 / G) tokens with all G heads of the group (R = TG * G <= 8
-// query rows); lanes own head-dim elements; closed slots stream row by row
-// with R online-softmax states.
+// fp32, on v_mfma_f32_32x32x2_f32 (operand forms: F32).  One workgroup = 32
+// query columns of one unit (token-major: column c is token c / G, head c % G),
+// whose four waves take every fourth 32-slot block of the closed slots straight
+// from the pages; their online-softmax states meet in LDS at the end.  The
+// wave with the fewest blocks starts from the open states, a product over the
+// raw prompt rows of the token block (exact: plus the carry record at its
+// start; windowed: of the up to three blocks the windows reach), with weight
+// omega for the rows of a column's open segment and 0 elsewhere:
+//   score(t) = sum_j w_tj (q_t . k_j) / z_t,   value(t) = sum_j w_tj v_j / z_t.
+// Bound by the longest tile's chain of blocks and the fp32 matrix rate: prompt
+// of 777 tokens, batch 3, 16/8 heads, d = 64: 906 -> 50 us against one wave per
+// 8 query rows on the vector ALUs (a cross-lane reduction per score).
 // ---------------------------------------------------------------------------
-template <int ES, int D, int G>
-__global__ __launch_bounds__(kThreads) void prompt_valu_kernel(PromptParams p, int ngroups) {
-  constexpr int TG = G >= 8 ? 1 : 8 / G;
-  constexpr int R = TG * G;
-  constexpr int E = D / 64;
-  constexpr int RB = D * ES;
-  constexpr int kAhead = 4;   // slot rows in flight
-  const int lane = threadIdx.x & 63;
-  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
-  const int u = wid / ngroups;
-  if (u >= p.units) return;
-  const int grp = wid - u * ngroups;
+template <int D, int G>
+__global__ __launch_bounds__(kThreads) void prompt_f32_kernel(PromptParams p, int ntiles) {
+  using F = F32<D>;
+  constexpr int T = 32 / G, NT = F::NT, RB = D * 4;
+  __shared__ __align__(16) float s_acc[F::kArea];
+  __shared__ float s_m[kWaves * 32], s_l[kWaves * 32];
+  const int ord = blockIdx.x / p.units, tile = ntiles - 1 - ord;   // latest tokens (most slots) first
+  const int u = (static_cast<int>(blockIdx.x) - ord * p.units + ord) % p.units;   // rotating over the XCDs
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, hb = lane >> 5;
   const int b = u / p.hkv, g = u - b * p.hkv;
   const int nb = clamp_prompt_len(p.prompt_lens, p.n, b);
-  const bool ok = p.page_base[u] >= 0;
-  const int a = grp * TG;
-  const int cnt = ok ? max(0, min(TG, nb - a)) : 0;
+  const int a = tile * T, cnt = p.page_base[u] >= 0 ? max(0, min(T, nb - a)) : 0;
+  const int tok = col / G, t = a + tok;
+  const bool colv = tok < cnt;
+  const int seg = cnt > 0 ? token_slots(p, u, a, cnt) : 0;
+  const int lim = colv ? __shfl(seg, tok, 64) : 0;   // this column sees slots < lim
+  const int top = __builtin_amdgcn_readfirstlane(cnt > 0 ? __shfl(seg, cnt - 1, 64) : 0);
+  const int lo = __builtin_amdgcn_readfirstlane(cnt > 0 ? __shfl(seg, 0, 64) : 0);   // every column sees slots < lo
+  const int nblk = (top + 31) >> 5;
 
-  float qr[R][E];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = r / G, h = r - j * G;
-#pragma unroll
-    for (int e = 0; e < E; ++e) qr[r][e] = 0.0f;
-    if (j < cnt)
-      load_e<ES, E>(static_cast<const char *>(p.q) +
-                        (b * p.qs[0] + int64_t(a + j) * p.qs[1] + (g * G + h) * p.qs[2] + lane * E) * ES,
-                    qr[r]);
-    if (lane == 0) qr[r][0] = 0.0f;   // q[0] is not part of the score
-  }
+  auto column = [&](const void *base, const int64_t *st, int c) {
+    return static_cast<const float *>(base) + b * st[0] + int64_t(a + c / G) * st[1] + (g * G + c % G) * st[2];
+  };
+  F::stage(s_acc, [&](int c) -> const float * { return c / G < cnt ? column(p.q, p.qs, c) : nullptr; }, true);
+  __syncthreads();
+  const float *qs = F::staged(s_acc, lane);
 
-  float m[R], l[R], acc[R][E];
+  float m = -1e30f, ls = 0.0f;
+  f32x16_t acc[NT];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    m[r] = 0.0f;
-    l[r] = 1.0f;
+  for (int i = 0; i < NT; ++i) acc[i] = f32x16_t{};
+
+  if (cnt > 0 && wave == (nblk & (kWaves - 1))) {   // open states
+    const uint8_t *al = p.alpha + int64_t(u) * p.max_prompt;
+    const float *om = p.omega + int64_t(u) * p.max_prompt;
+    const float *kbase = static_cast<const float *>(p.k) + b * p.ks[0] + g * p.ks[2];
+    const float *vbase = static_cast<const float *>(p.v) + b * p.vs[0] + g * p.vs[2];
+    // first token of column t's segment, as far as it lies in its 64-token
+    // chunk or the one before (-1: earlier)
+    const int cb = a & ~63, bs = a & ~31, W = p.window;
+    const unsigned long long here = __ballot(cb + lane < nb && al[min(cb + lane, nb - 1)] == 0);
+    const unsigned long long before = cb > 0 ? __ballot(al[cb - 64 + lane] == 0) : 0ull;
+    const unsigned long long upto = here & (~0ull >> (63 - (t & 63)));
+    const int start = upto ? cb + 63 - __clzll(static_cast<long long>(upto))
+                           : before ? cb - 1 - __clzll(static_cast<long long>(before)) : -1;
+    const int j0 = W > 0 ? max(max(start, t - W + 1), 0) : max(start, bs);
+    const bool carried = colv && W == 0 && start < bs;
+    const int ob0 = W > 0 ? max(a - W + 1, 0) >> 5 : a >> 5, ob1 = a >> 5;
+    auto tok_row = [&](const float *base, int64_t st, int j) { return base + min(j, nb - 1) * st; };
+    float part = 0.0f, zs = 0.0f;
+    bool left_out = false;
+#pragma unroll 1
+    for (int ob = ob0; ob <= ob1; ++ob) {
+      typename F::f4_t kr[F::NJ];
+      typename F::Cols vc;
+      auto value_row = [&](int i) { return tok_row(vbase, p.vs[1], ob * 32 + i); };
+      F::load_row(kr, tok_row(kbase, p.ks[1], ob * 32 + col), hb);
+      if (hb == 0) kr[0][0] = 0.0f;   // k_t[0] <- 0
+      vc.load(value_row, 0, lane);
+      float w[16];
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[r][e] = 0.0f;
-  }
-  int seg = -1, lim[TG];
-  if (cnt > 0) {
-    seg = token_slots(p, u, a, cnt);
-    auto snap = [&](int t, const float *ak, const float *av, float zs) {
-          const float inv = 1.0f / zs;
+      for (int r = 0; r < 16; ++r) w[r] = om[min(ob * 32 + F::row(r, hb), nb - 1)];
+      const f32x16_t sc = F::dots(kr, qs);
 #pragma unroll
-          for (int r = 0; r < R; ++r) {
-            if (a + r / G != t) continue;
-            float d = 0.0f;
-#pragma unroll
-            for (int e = 0; e < E; ++e) d = fmaf(qr[r][e], ak[e] * inv, d);
-            m[r] = wave_sum(d) * p.scale_log2;
-#pragma unroll
-            for (int e = 0; e < E; ++e) acc[r][e] = av[e] * inv;
-          }
-        };
-    if (p.window > 0)
-      walk_window_state<ES, D>(p, u, b, g, a, cnt, snap, [](int) {});
-    else
-      walk_open_state<ES, D>(p, u, b, g, a, cnt, snap, [](int) {});
-  }
-  int hi = 0;
-#pragma unroll
-  for (int j = 0; j < TG; ++j) {
-    const int sj = __shfl(seg, j, 64);
-    lim[j] = j < cnt ? sj : 0;
-    hi = max(hi, lim[j]);
-  }
-  const int P = 1 << p.log2p;
-  const int64_t pt = int64_t(u) * p.maxpages;
-  for (int s0 = 0; s0 < hi; s0 += kAhead) {
-    float kk[kAhead][E], vv[kAhead][E];
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      const int s = min(s0 + i, hi - 1);
-      const char *row = p.pool + int64_t(p.ptab[pt + (s >> p.log2p)]) * p.page_bytes +
-                        int64_t(s & (P - 1)) * RB + lane * E * ES;
-      load_e<ES, E>(row, kk[i]);
-      load_e<ES, E>(row + int64_t(P) * RB, vv[i]);
+      for (int r = 0; r < 16; ++r) {
+        const int j = ob * 32 + F::row(r, hb);
+        const bool in = colv && j >= j0 && j <= t;
+        part = in ? fmaf(w[r], sc[r], part) : part;
+        w[r] = in ? w[r] : 0.0f;
+        zs += w[r];
+      }
+      left_out |= F::template add_rows<true>(acc, vc, value_row, w, lane);
     }
+    if (__any(left_out)) {
+      for (int ob = ob0; ob <= ob1; ++ob)
+        F::add_nonfinite(acc, [&](int i) { return tok_row(vbase, p.vs[1], ob * 32 + i); },
+                         [&](int i) { return colv && ob * 32 + i >= j0 && ob * 32 + i <= t; }, lane);
+    }
+    if (__any(carried)) {   // the segment's sums before the block
+      const float *cr = p.carry + (int64_t(u) * p.carry_blocks + (bs >> 5)) * carry_stride(D);
+      if (carried) {
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      const int s = s0 + i;
-      if (s >= hi) break;
+        for (int j = 0; j < F::NJ; ++j) {
+          const typename F::f4_t c4 = *reinterpret_cast<const typename F::f4_t *>(cr + 8 * j + 4 * hb);
+          const typename F::f4_t q4 = *reinterpret_cast<const typename F::f4_t *>(qs + 8 * j);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (s >= lim[r / G]) continue;
-        float d = 0.0f;
+          for (int i = 0; i < 4; ++i) part = fmaf(q4[i], c4[i], part);
+        }
 #pragma unroll
-        for (int e = 0; e < E; ++e) d = fmaf(qr[r][e], kk[i][e], d);
-        const float x = wave_sum(d) * p.scale_log2;
-        const float mn = fmaxf(m[r], x);
-        const float f = fast_exp2(m[r] - mn), w = fast_exp2(x - mn);
-        l[r] = l[r] * f + w;
+        for (int r = 0; r < 16; ++r) {
+          const typename F::col_t e = *reinterpret_cast<const typename F::col_t *>(cr + D + NT * F::row(r, hb));
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc[r][e] = fmaf(acc[r][e], f, w * vv[i][e]);
-        m[r] = mn;
+          for (int i = 0; i < NT; ++i) acc[i][r] += e[i];
+        }
+        if (hb == 0) zs += cr[2 * D];
       }
     }
+    part += __shfl_xor(part, 32, 64);
+    zs += __shfl_xor(zs, 32, 64);
+    const float inv = colv ? 1.0f / zs : 0.0f;
+    if (colv) {
+      m = part * inv * p.scale_log2;
+      ls = hb == 0 ? 1.0f : 0.0f;   // the open state's weight, counted once per column
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) acc[i] *= inv;
   }
+
+  // Closed slots.  Lane `col` looks its slot's page up one block ahead; a group
+  // of eight slots lies in one page, whose number its first lane holds.
+  const int P = 1 << p.log2p;
+  const int32_t *pt = p.ptab + int64_t(u) * p.maxpages;
+  auto page_of = [&](int kb) { return pt[min(kb * 32 + col, top - 1) >> p.log2p]; };
+  typename F::f4_t kr[F::NJ];
+  int page = 0;
+  auto load_keys = [&](int kb, int pg) {
+    const int s = min(kb * 32 + col, top - 1);
+    F::load_row(kr, reinterpret_cast<const float *>(p.pool + int64_t(pg) * p.page_bytes + int64_t(s & (P - 1)) * RB), hb);
+  };
+  if (wave < nblk) {
+    page = page_of(wave);
+    load_keys(wave, page);
+  }
+  bool left_out = false;
+  auto value_row = [&](int kb, int pg, int i) {
+    const int q8 = i & ~7, pq = __builtin_amdgcn_readlane(pg, q8);
+    return reinterpret_cast<const float *>(p.pool + int64_t(pq) * p.page_bytes +
+                                           int64_t(P + ((kb * 32 + q8) & (P - 1)) + (i & 7)) * RB);
+  };
+  auto block = [&](int kb, auto masked_c) {
+    constexpr bool MASKED = decltype(masked_c)::value;   // slots that some column does not see
+    const int next = page_of(kb + kWaves);   // (past the last block: its last slot's page)
+    typename F::Cols vc;
+    auto vrow = [&](int i) { return value_row(kb, page, i); };
+    vc.load(vrow, 0, lane);
+    const f32x16_t sc = F::dots(kr, qs);
+    load_keys(kb + kWaves, next);
+    float x[16], mx = neg_inf();
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = r / G, h = r - j * G;
-    const int t = a + j;
-    if (t >= p.n) continue;
-    float o[E];
-    const float inv = j < cnt ? 1.0f / l[r] : 0.0f;
+    for (int r = 0; r < 16; ++r) {
+      x[r] = sc[r] * p.scale_log2;
+      if (MASKED && kb * 32 + F::row(r, hb) >= lim) x[r] = neg_inf();
+      mx = fmaxf(mx, x[r]);
+    }
+    const float mn = fmaxf(m, max_halves(mx));
+    const float f = fast_exp2(m - mn);
+    m = mn;
+    ls *= f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = acc[r][e] * inv;
-    store_e<ES, E>(static_cast<char *>(p.out) +
-                       (b * p.os[0] + int64_t(t) * p.os[1] + (g * G + h) * p.os[2] + lane * E) * ES,
-                   o);
+    for (int i = 0; i < NT; ++i) acc[i] *= f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      x[r] = fast_exp2(x[r] - mn);
+      ls += x[r];
+    }
+    left_out |= F::template add_rows<MASKED>(acc, vc, vrow, x, lane);
+    page = next;
+  };
+  int kb = wave;
+#pragma unroll 1
+  for (; kb < (lo >> 5); kb += kWaves) block(kb, std::false_type{});
+#pragma unroll 1
+  for (; kb < nblk; kb += kWaves) block(kb, std::true_type{});
+  if (__any(left_out)) {
+    for (kb = (lo >> 5); kb < nblk; ++kb) {
+      if ((kb & (kWaves - 1)) != wave) continue;
+      const int pg = page_of(kb);
+      F::add_nonfinite(acc, [&](int i) { return value_row(kb, pg, i); },
+                       [&](int i) { return kb * 32 + i < lim; }, lane);
+    }
+  }
+
+  ls += __shfl_xor(ls, 32, 64);
+  if (hb == 0) {
+    s_m[wave * 32 + col] = m;
+    s_l[wave * 32 + col] = ls;
+  }
+  __syncthreads();
+  float M = s_m[col], L = 0.0f;
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) M = fmaxf(M, s_m[w * 32 + col]);
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) L += s_l[w * 32 + col] * fast_exp2(s_m[w * 32 + col] - M);
+  const float f = fast_exp2(m - M) / L;
+#pragma unroll
+  for (int i = 0; i < NT; ++i) acc[i] *= f;
+  F::put(s_acc, wave, lane, acc);   // (every wave is past its last use of the staged rows)
+  __syncthreads();
+  for (int i = tid; i < 32 * D / 4; i += kThreads) {
+    const int c = i / (D / 4), e = i % (D / 4);
+    if (a + c / G < p.n)   // (zeros past the prompt)
+      *reinterpret_cast<typename F::f4_t *>(const_cast<float *>(column(p.out, p.os, c)) + 4 * e) =
+          c / G < cnt ? F::sum(s_acc, c, e) : typename F::f4_t{};
   }
 }
 
@@ -938,15 +963,12 @@ hipError_t prompt_mfma(const PromptParams &p, bool vt, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int ES, int D, int G>
-hipError_t prompt_valu(const PromptParams &p, hipStream_t s) {
-  constexpr int TG = G >= 8 ? 1 : 8 / G;
-  const int ngroups = (p.n + TG - 1) / TG;
-  const int64_t waves = int64_t(p.units) * ngroups;
-  const int64_t blocks = (waves + kWaves - 1) / kWaves;
+template <int D, int G>
+hipError_t prompt_f32(const PromptParams &p, hipStream_t s) {
+  const int ntiles = (p.n + 32 / G - 1) / (32 / G);
+  const int64_t blocks = int64_t(p.units) * ntiles;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((prompt_valu_kernel<ES, D, G>), dim3(unsigned(blocks)), dim3(kThreads), 0, s,
-                     p, ngroups);
+  hipLaunchKernelGGL((prompt_f32_kernel<D, G>), dim3(unsigned(blocks)), dim3(kThreads), 0, s, p, ntiles);
   return hipGetLastError();
 }
 
@@ -965,10 +987,10 @@ hipError_t prompt_by_group(int group, bool vt, const PromptParams &p, const Cont
   } else {
     (void)vt;
     switch (group) {
-      case 1: return prompt_valu<ES, D, 1>(p, s);
-      case 2: return prompt_valu<ES, D, 2>(p, s);
-      case 4: return prompt_valu<ES, D, 4>(p, s);
-      case 8: return prompt_valu<ES, D, 8>(p, s);
+      case 1: return prompt_f32<D, 1>(p, s);
+      case 2: return prompt_f32<D, 2>(p, s);
+      case 4: return prompt_f32<D, 4>(p, s);
+      case 8: return prompt_f32<D, 8>(p, s);
       default: return hipErrorInvalidValue;
     }
   }
