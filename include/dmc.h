@@ -208,9 +208,9 @@ dmc_status dmc_prefill_attend(dmc_cache *cache, int32_t layer,
  *     (-1 when it was dropped for lack of capacity).
  * The call only enqueues kernels on `stream` (no allocation, no host
  * synchronisation, no memset), so it can be captured in a HIP graph.  Every
- * call on a layer uses the same device buffers (its last kernel copies the
- * post-step lengths back into the layer's current-lengths buffer), so a
- * captured step can be replayed any number of times. */
+ * call on a layer uses the same device buffers (it leaves the post-step
+ * lengths in the layer's current-lengths buffer), so a captured step can be
+ * replayed any number of times. */
 dmc_status dmc_decode_step(dmc_cache *cache, int32_t layer, const void *q_dev,
                            const void *k_dev, const void *v_dev, void *out_dev,
                            int32_t *slot_index_dev, dmc_stream_t stream);

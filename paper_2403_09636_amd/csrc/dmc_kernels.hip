@@ -274,8 +274,13 @@ __device__ __forceinline__ int unit_at(const DecodeParams &p, const int *s_off, 
   return u0 + jl;
 }
 
-template <int ES, int D, int G, bool WIN, bool GRP>
+// UNIT: one workgroup per unit (short caches, see decode_impl).  Its waves take
+// equal runs of the closed slots, their states meet in LDS, and the owner (wave
+// 0) writes the output and the unit's new length: no slot-space table, no
+// partial records, no combine launch.
+template <int ES, int D, int G, bool WIN, bool GRP, bool UNIT>
 __global__ __launch_bounds__((valu_decode_threads<ES, G>())) void decode_kernel(DecodeParams p) {
+  static_assert(!(UNIT && GRP), "one workgroup per unit needs no table");
   constexpr int NT = valu_decode_threads<ES, G>(), NW = NT / 64;   // threads, waves per workgroup
   using V = V16<ES>;
   constexpr int VN = V::N;        // elements per 16-byte lane chunk
@@ -298,28 +303,43 @@ __global__ __launch_bounds__((valu_decode_threads<ES, G>())) void decode_kernel(
   const int log2cs = p.log2p < kLog2Chunk ? p.log2p : kLog2Chunk;
 
   constexpr int OVH = kValuUnitOverhead;
-  const int S = build_slot_space<GRP, OVH, NT>(p, s_off, s_wsum);
-  const int nwaves = gridDim.x * NW;
-  int span = (S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves);   // equal shares
-  if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
-  const int nranges = (S + span - 1) / span;
+  __shared__ __align__(16) float s_state[UNIT ? NW * G * REC : 4];   // the waves' states (UNIT)
+  int S = 0, nwaves = 0, span = 1, nranges = 1;
+  if constexpr (!UNIT) {
+    S = build_slot_space<GRP, OVH, NT>(p, s_off, s_wsum);
+    nwaves = gridDim.x * NW;
+    span = (S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves);   // equal shares
+    if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
+    nranges = (S + span - 1) / span;
+  }
 
-  for (int r = blockIdx.x * NW + wave; r < nranges; r += nwaves) {
-    int pos = r * span;
-    const int pos_end = min(pos + span, S);
-    int off;   // the piece's unit's offset; a later piece of the range starts its unit
-    for (int u = unit_at<GRP, OVH>(p, s_off, pos, off); pos < pos_end; ++u, off = pos) {
-      if constexpr (!GRP) off = s_off[u];
-      const int n_u = GRP ? max(p.len_in[u], 1) + OVH : s_off[u + 1] - off;
-      const int start = pos - off;
-      const int stop = min(pos_end, off + n_u) - off;   // this piece: [start, stop)
-      pos = off + stop;
-      const bool owner = stop == n_u;                   // holds the open slot
+  for (int r = UNIT ? 0 : blockIdx.x * NW + wave; r < nranges; r += UNIT ? 1 : nwaves) {
+    int pos = UNIT ? 0 : r * span;
+    const int pos_end = UNIT ? 1 : min(pos + span, S);
+    int off = 0;   // the piece's unit's offset; a later piece of the range starts its unit
+    for (int u = UNIT ? int(blockIdx.x) : unit_at<GRP, OVH>(p, s_off, pos, off); pos < pos_end; ++u, off = pos) {
       const int l = p.len_in[u];
+      int start, end;    // the piece's closed slots
+      bool owner;        // the piece holds the open slot
+      if constexpr (UNIT) {
+        // equal runs of whole chunks (the open slot, l - 1, is the owner's)
+        const int chunks = (max(l - 1, 0) + CS - 1) >> log2cs;
+        start = (wave * chunks / NW) << log2cs;
+        end = min(((wave + 1) * chunks / NW) << log2cs, max(l - 1, 0));
+        owner = wave == 0;
+        pos = 1;
+      } else {
+        if constexpr (!GRP) off = s_off[u];
+        const int n_u = GRP ? max(l, 1) + OVH : s_off[u + 1] - off;
+        start = pos - off;
+        const int stop = min(pos_end, off + n_u) - off;   // this piece: [start, stop)
+        pos = off + stop;
+        owner = stop == n_u;
+        // the open slot and the virtual tail are not streamed
+        end = min(owner ? n_u - 1 : stop, n_u - OVH - 1);
+      }
       const int b = u / p.hkv, g = u - b * p.hkv;
       const int64_t pt = int64_t(u) * p.maxpages;
-      // closed slots [start, end): the open slot and the virtual tail are not streamed
-      int end = min(owner ? n_u - 1 : stop, n_u - OVH - 1);
 
       // The unit's query heads (this lane's slice), element 0 zeroed.  Scores
       // are scaled by log2(e)/sqrt(d) after the row sum.
@@ -459,6 +479,33 @@ __global__ __launch_bounds__((valu_decode_threads<ES, G>())) void decode_kernel(
           merge_state<VN>(m[h], ls[h], acc[h], m2, l2, a2);
         }
       }
+      if constexpr (UNIT) {   // the waves' states meet in the owner
+        if (!owner && grp == 0) {
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            float *rec = s_state + (wave * G + h) * REC;
+            if (part == 0) {
+              rec[0] = m[h];
+              rec[1] = ls[h];
+            }
+#pragma unroll
+            for (int e = 0; e < VN; ++e) rec[4 + part * VN + e] = acc[h][e];
+          }
+        }
+        __syncthreads();   // (every wave has also read the unit's length)
+        if (!owner) return;
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            const float *rec = s_state + (w * G + h) * REC;
+            float a2[VN];
+#pragma unroll
+            for (int e = 0; e < VN; ++e) a2[e] = rec[4 + part * VN + e];
+            merge_state<VN>(m[h], ls[h], acc[h], rec[0], rec[1], a2);
+          }
+        }
+      }
 
       if (owner) {
         // Algorithm 1 for unit u: alpha from k[0] (the first token of an empty
@@ -558,17 +605,19 @@ __global__ __launch_bounds__((valu_decode_threads<ES, G>())) void decode_kernel(
         }
         if (lane == 0) {
           if (has_cur) p.z[u] = znew;
-          p.len_out[u] = (has_cur && !alpha) ? l + 1 : l;
+          (UNIT ? p.len_in : p.len_out)[u] = (has_cur && !alpha) ? l + 1 : l;
           if (p.slot_index) p.slot_index[u] = has_cur ? slot : -1;
           if (flag) atomicOr(&p.ctrl->flags, flag);
-          const int r0 = off / span;                  // range holding the unit's first slot
-          p.meta[2 * u] = r0 + u;                     // its first partial record
-          p.meta[2 * u + 1] = r - r0 + 1;             // number of pieces
+          if constexpr (!UNIT) {
+            const int r0 = off / span;                  // range holding the unit's first slot
+            p.meta[2 * u] = r0 + u;                     // its first partial record
+            p.meta[2 * u + 1] = r - r0 + 1;             // number of pieces
+          }
         }
       }
 
       if (grp == 0) {
-        if (start == 0 && owner) {     // the whole unit in one piece: final output
+        if (UNIT || (start == 0 && owner)) {   // the whole unit: final output
 #pragma unroll
           for (int h = 0; h < G; ++h) {
             const float inv = ls[h] > 0.0f ? 1.0f / ls[h] : 0.0f;
@@ -698,8 +747,10 @@ constexpr int mfma_ring_bytes() { return kWaves * 2 * 2 * 32 * D * 2; }   // 2 s
 template <int D>
 constexpr int mfma_decode_wg_per_cu() { return D == 128 ? 1 : 2; }
 
-template <int D, int G, bool WIN, bool GRP>
+// UNIT: one workgroup per unit, as in decode_kernel.
+template <int D, int G, bool WIN, bool GRP, bool UNIT>
 __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_mfma_kernel(DecodeParams p) {
+  static_assert(!(UNIT && GRP), "one workgroup per unit needs no table");
   constexpr int KS = D / 32;      // k-steps of the score product
   constexpr int NT = D / 16;      // 16-dim tiles of the value product
   constexpr int RB = D * 2;       // bytes per key row
@@ -719,7 +770,8 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
   const int U = p.units;
   int *s_off = reinterpret_cast<int *>(smem);
   const int ng = GRP ? (U + p.slot_group - 1) / p.slot_group : U;   // slot-space table entries - 1
-  const size_t win_lds_off = align_up(size_t(ng + 1) * 4, 16);   // windowed means, 2 D fp32 per wave
+  const size_t win_lds_off = UNIT ? 0 : align_up(size_t(ng + 1) * 4, 16);   // windowed means, 2 D fp32 per wave
+  __shared__ __align__(16) float s_state[UNIT ? kWaves * G * REC : 4];     // the waves' states (UNIT)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, q = lane >> 4;      // MFMA column (head or dim) and k-group
   const int P = 1 << p.log2p;
@@ -727,54 +779,73 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
   const uint4 zero4 = make_uint4(0, 0, 0, 0);
 
   constexpr int OVH = kMfmaUnitOverhead;
-  const int S = build_slot_space<GRP, OVH>(p, s_off, s_wsum);
-  const int nwaves = gridDim.x * kWaves;
-  int span = (S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves);
-  if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
-  // Whole units when that balances: wave w takes units [w U / W, (w + 1) U / W)
-  // in full if no wave's share then exceeds the equal slot share by more than
-  // kWholeUnitSlack.  Split units cost this kernel a piece start, an owner
-  // epilogue and a partial record each (measured: a 70B-shaped layer of
-  // lengths 2048 +- 32 at 407-426 us per call against 345-348 us at 2048
-  // exactly), so near-uniform lengths -- one compression ratio for every head
-  // -- stream faster without them.  Grouped tables and forced split sizes keep
-  // the equal-slot ranges.
+  int S = 0, nwaves = 0, span = 1, nranges = 1;
   bool whole = false;
-  if constexpr (!GRP) {
-    if (p.split_tile == 0 && U >= nwaves) {
-      int mx = 0;
-      for (int w = threadIdx.x; w < nwaves; w += kThreads) {
-        const int u0 = static_cast<int>(int64_t(w) * U / nwaves);
-        const int u1 = static_cast<int>(int64_t(w + 1) * U / nwaves);
-        mx = max(mx, s_off[u1] - s_off[u0]);
-      }
+  if constexpr (!UNIT) {
+    S = build_slot_space<GRP, OVH>(p, s_off, s_wsum);
+    nwaves = gridDim.x * kWaves;
+    span = (S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves);
+    if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
+    // Whole units when that balances: wave w takes units [w U / W, (w + 1) U / W)
+    // in full if no wave's share then exceeds the equal slot share by more than
+    // kWholeUnitSlack.  Split units cost this kernel a piece start, an owner
+    // epilogue and a partial record each (measured: a 70B-shaped layer of
+    // lengths 2048 +- 32 at 407-426 us per call against 345-348 us at 2048
+    // exactly), so near-uniform lengths -- one compression ratio for every head
+    // -- stream faster without them.  Grouped tables and forced split sizes keep
+    // the equal-slot ranges.
+    if constexpr (!GRP) {
+      if (p.split_tile == 0 && U >= nwaves) {
+        int mx = 0;
+        for (int w = threadIdx.x; w < nwaves; w += kThreads) {
+          const int u0 = static_cast<int>(int64_t(w) * U / nwaves);
+          const int u1 = static_cast<int>(int64_t(w + 1) * U / nwaves);
+          mx = max(mx, s_off[u1] - s_off[u0]);
+        }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
-      if (lane == 0) s_wsum[wave] = mx;
-      __syncthreads();
-      for (int w = 0; w < kWaves; ++w) mx = max(mx, s_wsum[w]);
-      whole = int64_t(mx) * 100 <= int64_t(span) * (100 + kWholeUnitSlack);
+        for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+        if (lane == 0) s_wsum[wave] = mx;
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w) mx = max(mx, s_wsum[w]);
+        whole = int64_t(mx) * 100 <= int64_t(span) * (100 + kWholeUnitSlack);
+      }
     }
+    nranges = whole ? nwaves : (S + span - 1) / span;
   }
-  const int nranges = whole ? nwaves : (S + span - 1) / span;
 
-  for (int r = blockIdx.x * kWaves + wave; r < nranges; r += nwaves) {
+  for (int r = UNIT ? 0 : blockIdx.x * kWaves + wave; r < nranges; r += UNIT ? 1 : nwaves) {
     const int wu0 = whole ? static_cast<int>(int64_t(r) * U / nwaves) : 0;
-    int pos = whole ? s_off[wu0] : r * span;
-    const int pos_end = whole ? s_off[static_cast<int>(int64_t(r + 1) * U / nwaves)] : min(pos + span, S);
-    int off;
-    for (int u = whole ? (off = pos, wu0) : unit_at<GRP, OVH>(p, s_off, pos, off); pos < pos_end;
-         ++u, off = pos) {
-      if constexpr (!GRP) off = s_off[u];
-      const int n_u = GRP ? max(p.len_in[u], 1) + OVH : s_off[u + 1] - off;
-      const int start = pos - off;
-      const int stop = min(pos_end, off + n_u) - off;
-      pos = off + stop;
-      const bool owner = stop == n_u;
+    int pos = UNIT ? 0 : whole ? s_off[wu0] : r * span;
+    const int pos_end = UNIT    ? 1
+                        : whole ? s_off[static_cast<int>(int64_t(r + 1) * U / nwaves)]
+                                : min(pos + span, S);
+    int off = 0;
+    for (int u = UNIT    ? int(blockIdx.x)
+                 : whole ? (off = pos, wu0)
+                         : unit_at<GRP, OVH>(p, s_off, pos, off);
+         pos < pos_end; ++u, off = pos) {
       const int l = p.len_in[u];
+      int start, end;   // closed slots of the piece
+      bool owner;
+      if constexpr (UNIT) {
+        // equal runs of whole chunks; the owner is the wave with the last chunk,
+        // whose page holds the open slot 31 times in 32
+        const int chunks = (max(l - 1, 0) + 31) >> 5;
+        start = (wave * chunks / kWaves) << 5;
+        end = min(((wave + 1) * chunks / kWaves) << 5, max(l - 1, 0));
+        owner = wave == kWaves - 1;
+        pos = 1;
+      } else {
+        if constexpr (!GRP) off = s_off[u];
+        const int n_u = GRP ? max(l, 1) + OVH : s_off[u + 1] - off;
+        start = pos - off;
+        const int stop = min(pos_end, off + n_u) - off;
+        pos = off + stop;
+        owner = stop == n_u;
+        end = min(owner ? n_u - 1 : stop, n_u - OVH - 1);   // closed slots
+      }
       const int b = u / p.hkv, g = u - b * p.hkv;
       const int64_t pt = int64_t(u) * p.maxpages;
-      const int end = min(owner ? n_u - 1 : stop, n_u - OVH - 1);   // closed slots
 
       // Q^T operand: lane (n, q) holds Q[head n][32 ks + 8q .. +8]; heads >= G are 0.
       uint4 qb[KS];
@@ -967,6 +1038,41 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         }
       }
 
+      if constexpr (UNIT) {   // the waves' states meet in the owner
+        if (!owner) {
+          ls += __shfl_xor(ls, 16, 64);
+          ls += __shfl_xor(ls, 32, 64);
+          if (n < G) {
+            float *rec = s_state + (wave * G + n) * REC;
+            if (q == 0) {
+              rec[0] = m;
+              rec[1] = ls;
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+              *reinterpret_cast<float4 *>(rec + 4 + 16 * nt + 4 * q) =
+                  make_float4(acc[nt][0], acc[nt][1], acc[nt][2], acc[nt][3]);
+          }
+        }
+        __syncthreads();   // (every wave has also read the unit's length)
+        if (!owner) return;
+#pragma unroll 1
+        for (int w = 0; w < kWaves - 1; ++w) {
+          const float *rec = s_state + (w * G + (n < G ? n : 0)) * REC;
+          const float m2 = rec[0], mn = fmaxf(m, m2);
+          if (n < G && mn != neg_inf()) {   // (the record's sum counted in one of the column's four lanes)
+            const float f1 = fast_exp2(m - mn), f2 = fast_exp2(m2 - mn);
+            ls = ls * f1 + (q == 0 ? rec[1] * f2 : 0.0f);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              const float4 x = *reinterpret_cast<const float4 *>(rec + 4 + 16 * nt + 4 * q);
+              acc[nt] = acc[nt] * f1 + f32x4_t{x.x, x.y, x.z, x.w} * f2;
+            }
+            m = mn;
+          }
+        }
+      }
+
       // Owner: the open slot copied from the ring above, else from its page.
       int seg_len = 0;
       if (owner) {
@@ -1112,19 +1218,21 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         values(sraw, va, (old_valid ? 1u : 0u) | (has_cur ? 2u : 0u));
         if (lane == 0) {
           if (has_cur) p.z[u] = znew;
-          p.len_out[u] = (has_cur && !alpha) ? l + 1 : l;
+          (UNIT ? p.len_in : p.len_out)[u] = (has_cur && !alpha) ? l + 1 : l;
           if (p.slot_index) p.slot_index[u] = has_cur ? slot : -1;
           if (flag) atomicOr(&p.ctrl->flags, flag);
-          const int r0 = whole ? r : off / span;
-          p.meta[2 * u] = r0 + u;
-          p.meta[2 * u + 1] = r - r0 + 1;
+          if constexpr (!UNIT) {
+            const int r0 = whole ? r : off / span;
+            p.meta[2 * u] = r0 + u;
+            p.meta[2 * u + 1] = r - r0 + 1;
+          }
         }
       }
 
       ls += __shfl_xor(ls, 16, 64);
       ls += __shfl_xor(ls, 32, 64);
       if (n < G) {
-        if (start == 0 && owner) {     // the whole unit in one piece: final output
+        if (UNIT || (start == 0 && owner)) {   // the whole unit: final output
           const float inv = ls > 0.0f ? 1.0f / ls : 0.0f;
           uint16_t *op = static_cast<uint16_t *>(p.out) + int64_t(b * p.hq + g * G + n) * D + 4 * q;
 #pragma unroll
@@ -2169,26 +2277,44 @@ hipError_t launch_transpose(char *pool, int64_t page_bytes, const Control *ctrl,
   return hipGetLastError();
 }
 
-template <int ES, int D, int G, bool WIN, bool GRP>
+template <int ES, int D, int G, bool WIN, bool GRP, bool UNIT = false>
 void launch_decode_kernel(const DecodeParams &p, int grid, bool vt, size_t lds, hipStream_t s) {
   if constexpr (ES == 2 && G >= 4) {
     if (vt) {
-      hipLaunchKernelGGL((decode_mfma_kernel<D, G, WIN, GRP>), dim3(grid), dim3(kThreads), lds, s, p);
+      hipLaunchKernelGGL((decode_mfma_kernel<D, G, WIN, GRP, UNIT>), dim3(grid), dim3(kThreads), lds, s, p);
       return;
     }
   }
   // grid counts workgroups of kThreads; the vector kernel packs the same waves
   // into workgroups of valu_decode_threads<ES, G>()
   constexpr int NT = valu_decode_threads<ES, G>();
-  const int vgrid = std::max(1, grid / (NT / kThreads));
-  hipLaunchKernelGGL((decode_kernel<ES, D, G, WIN, GRP>), dim3(vgrid), dim3(NT), lds, s, p);
+  const int vgrid = UNIT ? grid : std::max(1, grid / (NT / kThreads));
+  hipLaunchKernelGGL((decode_kernel<ES, D, G, WIN, GRP, UNIT>), dim3(vgrid), dim3(NT), lds, s, p);
 }
+
+// Largest K and V bytes of a unit at capacity, and units, for which a decode
+// step runs as one workgroup per unit.  One compute unit streams about 50 KB/us
+// (measured, 4 or 16 waves), so the longest unit of 256 KB takes 5 us, which is
+// what the slot-space table and the combine launch of the general path cost; and
+// up to 256 units the workgroups are all resident at once, one per compute unit.
+// Four fp32 units of up to 64 slots: 5.3 + 7.8 (combine) -> 3.8 us per step.
+constexpr int64_t kUnitBytes = 256 << 10;
+constexpr int kUnitMaxUnits = 256;
 
 template <int ES, int D, int G>
 hipError_t decode_impl(const DecodeParams &p, int grid, bool vt, hipStream_t s) {
   const size_t lds = decode_lds_bytes((p.units + p.slot_group - 1) / p.slot_group + 1, G, D,
                                       p.win.window > 0);
   if (vt && !(ES == 2 && G >= 4)) return hipErrorInvalidValue;
+  // Short caches: one workgroup per unit, one launch per step.
+  if (p.split_tile == 0 && p.units <= kUnitMaxUnits && int64_t(p.max_slots) * 2 * D * ES <= kUnitBytes) {
+    const size_t unit_lds = decode_lds_bytes(0, G, D, p.win.window > 0);
+    if (p.win.window > 0)
+      launch_decode_kernel<ES, D, G, true, false, true>(p, p.units, vt, unit_lds, s);
+    else
+      launch_decode_kernel<ES, D, G, false, false, true>(p, p.units, vt, unit_lds, s);
+    return hipGetLastError();
+  }
   // The matrix-core kernel adds its chunk ring to the LDS of a workgroup.  When
   // two such workgroups do not fit a compute unit (always at d = 128), the grid
   // is halved so that every workgroup is resident at once.
