@@ -73,6 +73,9 @@ constexpr int kRangesPerWave = 1;   // slot-space ranges per decode wave (2 and 
 // two units of 2000+ slots (no change measured).  At most kDecodeUnitOverhead.
 constexpr int kValuUnitOverhead = 32;
 constexpr int kMfmaUnitOverhead = 0;
+// Fewest positions per range: on a short layer, where equal shares would be
+// a few slots, every range still pays its round trips and a partial record.
+constexpr int kMinSpan = 64;
 // Largest excess, in percent of the equal slot share, at which the matrix-core
 // decode gives every wave whole units instead of equal slot ranges.
 constexpr int kWholeUnitSlack = 10;
@@ -308,12 +311,14 @@ __global__ __launch_bounds__((valu_decode_threads<ES, G>())) void decode_kernel(
   if constexpr (!UNIT) {
     S = build_slot_space<GRP, OVH, NT>(p, s_off, s_wsum);
     nwaves = gridDim.x * NW;
-    span = (S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves);   // equal shares
+    span = max((S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves), kMinSpan);   // equal shares
     if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
     nranges = (S + span - 1) / span;
   }
 
-  for (int r = UNIT ? 0 : blockIdx.x * NW + wave; r < nranges; r += UNIT ? 1 : nwaves) {
+  // (few ranges: one per workgroup before the second of any)
+  const int r_first = UNIT ? 0 : 2 * nranges <= nwaves ? wave * gridDim.x + blockIdx.x : blockIdx.x * NW + wave;
+  for (int r = r_first; r < nranges; r += UNIT ? 1 : nwaves) {
     int pos = UNIT ? 0 : r * span;
     const int pos_end = UNIT ? 1 : min(pos + span, S);
     int off = 0;   // the piece's unit's offset; a later piece of the range starts its unit
@@ -784,7 +789,7 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
   if constexpr (!UNIT) {
     S = build_slot_space<GRP, OVH>(p, s_off, s_wsum);
     nwaves = gridDim.x * kWaves;
-    span = (S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves);
+    span = max((S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves), kMinSpan);
     if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
     // Whole units when that balances: wave w takes units [w U / W, (w + 1) U / W)
     // in full if no wave's share then exceeds the equal slot share by more than
@@ -813,7 +818,9 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
     nranges = whole ? nwaves : (S + span - 1) / span;
   }
 
-  for (int r = UNIT ? 0 : blockIdx.x * kWaves + wave; r < nranges; r += UNIT ? 1 : nwaves) {
+  // (few ranges: one per workgroup before the second of any)
+  const int r_first = UNIT ? 0 : 2 * nranges <= nwaves ? wave * gridDim.x + blockIdx.x : blockIdx.x * kWaves + wave;
+  for (int r = r_first; r < nranges; r += UNIT ? 1 : nwaves) {
     const int wu0 = whole ? static_cast<int>(int64_t(r) * U / nwaves) : 0;
     int pos = UNIT ? 0 : whole ? s_off[wu0] : r * span;
     const int pos_end = UNIT    ? 1
@@ -1257,108 +1264,102 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
   }
 }
 
-// Combine the split-K partial records of units with more than one tile:
+// Combine the split-K partial records of units with more than one piece:
 // o = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i.  One wave per
-// (b, query head); lane i fetches record i's max and sum, then every lane
-// accumulates its E dims over the records.  The launch also copies the
+// (b, query head), lanes own E dims each.  Bound by latency: the records are read
+// R at a time, every load of a batch in one round trip (lane i < R reads record
+// i's max and sum, broadcast by v_readlane), R = 4 for the usual case, 8, or
+// batches of 16.  Short and uneven layers split their long units into tens of
+// pieces; they have few heads, so there (WIDE) a workgroup's four waves share a
+// head's batches and merge in LDS.  One chat request (32 heads, up to 60 records
+// before ranges had a least size, 17 since): 13.3 -> 4.8 us per launch; 240
+// uneven heads, up to 61 records: about 7.9 -> 4.4 us.  The launch also copies the
 // step's post-update lengths back into the layer's current-lengths buffer
 // (every unit's owner wrote len_out; this launch runs after all of them).
-template <int ES, int D, int G>
+template <int ES, int D, int G, bool WIDE>
 __global__ __launch_bounds__(kThreads) void combine_kernel(DecodeParams p, int batch) {
   constexpr int REC = D + 4;
   constexpr int E = D / 64;
+  __shared__ float s_state[WIDE ? kWaves * (D + 2) : 1];
   {
     const int i = blockIdx.x * kThreads + threadIdx.x;
     if (i < p.units) p.len_in[i] = p.len_out[i];
   }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int bh = blockIdx.x * kWaves + wave;
+  const int bh = WIDE ? blockIdx.x : blockIdx.x * kWaves + wave;
   if (bh >= batch * p.hq) return;
   const int b = bh / p.hq, h = bh - b * p.hq;
   const int g = h / G, hg = h - g * G;
   const int u = b * p.hkv + g;
-  const int first = p.meta[2 * u], nt = p.meta[2 * u + 1];   // records first .. first+nt-1
+  // records first .. first + nt - 1 (wave-uniform; workgroup-uniform when WIDE)
+  const int first = __builtin_amdgcn_readfirstlane(p.meta[2 * u]);
+  const int nt = __builtin_amdgcn_readfirstlane(p.meta[2 * u + 1]);
   if (nt <= 1) return;
-  if (nt <= 4) {
-    // Few records (the usual case): every load is issued at once, one round trip.
-    float mi[4], li[4], a[4][E];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      mi[i] = neg_inf();
-      li[i] = 0.0f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) a[i][e] = 0.0f;
-      if (i < nt) {
-        const float *rec = p.partials + (int64_t(first + i) * G + hg) * REC;
-        mi[i] = rec[0];
-        li[i] = rec[1];
-#pragma unroll
-        for (int e = 0; e < E; ++e) a[i][e] = rec[4 + lane * E + e];
-      }
-    }
-    const float M = fmaxf(fmaxf(mi[0], mi[1]), fmaxf(mi[2], mi[3]));
-    float L = 0.0f, A[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) A[e] = 0.0f;
-    if (M != neg_inf()) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float w = mi[i] == neg_inf() ? 0.0f : fast_exp2(mi[i] - M);
-        L = fmaf(w, li[i], L);
-#pragma unroll
-        for (int e = 0; e < E; ++e) A[e] = fmaf(w, a[i][e], A[e]);
-      }
-    }
-    const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) A[e] *= inv;
-    store_e<ES, E>(static_cast<char *>(p.out) + (int64_t(bh) * D + lane * E) * ES, A);
-    return;
-  }
-  float L = 0.0f, A[E];
+  if (WIDE && nt <= 16 && wave > 0) return;   // one batch
+  const float *recs = p.partials + (int64_t(first) * G + hg) * REC;
+  float M = neg_inf(), L = 0.0f, A[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) A[e] = 0.0f;
-  float M = neg_inf();
-  for (int i0 = 0; i0 < nt; i0 += 64) {           // running max over chunks of 64 records
-    const int i = i0 + lane;
-    const float mi = i < nt ? p.partials[(int64_t(first + i) * G + hg) * REC] : neg_inf();
-    float mc = mi;
+  auto of_lane = [](float x, int j) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), j));
+  };
+  auto batches = [&](auto r_c, int i0, int step) {
+    constexpr int R = decltype(r_c)::value;
+    for (; i0 < nt; i0 += step) {
+      const int cnt = min(R, nt - i0);
+      const float *rb = recs + int64_t(i0) * G * REC;
+      const float *mine = rb + int64_t(min(lane, cnt - 1)) * G * REC;
+      const float mr = mine[0], lr = mine[1];
+      float a[R][E];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mc = fmaxf(mc, __shfl_xor(mc, o, 64));
-    const float mn = fmaxf(M, mc);
-    if (mn == neg_inf()) continue;
-    const float sc = fast_exp2(M - mn);
-    L *= sc;
+      for (int j = 0; j < R; ++j) {
+        const float *rec = rb + int64_t(min(j, cnt - 1)) * G * REC + 4 + lane * E;
 #pragma unroll
-    for (int e = 0; e < E; ++e) A[e] *= sc;
-    M = mn;
-    const float wi = i < nt ? fast_exp2(mi - M) : 0.0f;
-    const float li = i < nt ? p.partials[(int64_t(first + i) * G + hg) * REC + 1] : 0.0f;
-    float lw = wi * li;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lw += __shfl_xor(lw, o, 64);
-    L += lw;
-    const int cnt = min(64, nt - i0);
-    int j = 0;
-    for (; j + 4 <= cnt; j += 4) {
-      float w4[4], a4[4][E];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        w4[q] = __shfl(wi, j + q, 64);
-        const float *rec = p.partials + (int64_t(first + i0 + j + q) * G + hg) * REC + 4 + lane * E;
-#pragma unroll
-        for (int e = 0; e < E; ++e) a4[q][e] = rec[e];
+        for (int e = 0; e < E; ++e) a[j][e] = rec[e];
       }
+      const float mi = lane < cnt ? mr : neg_inf();
+      float mn = M;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int j = 0; j < R; ++j) mn = fmaxf(mn, of_lane(mi, j));
+      if (mn == neg_inf()) continue;
+      const float sc = fast_exp2(M - mn);
+      M = mn;
+      const float wi = lane < cnt ? fast_exp2(mi - mn) : 0.0f;
+      const float wl = lane < cnt ? wi * lr : 0.0f;
+      L *= sc;
 #pragma unroll
-        for (int e = 0; e < E; ++e) A[e] = fmaf(w4[q], a4[q][e], A[e]);
+      for (int e = 0; e < E; ++e) A[e] *= sc;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        if (j < cnt) {
+          const float w = of_lane(wi, j);
+          L += of_lane(wl, j);
+#pragma unroll
+          for (int e = 0; e < E; ++e) A[e] = fmaf(w, a[j][e], A[e]);
+        }
+      }
     }
-    for (; j < cnt; ++j) {
-      const float w = __shfl(wi, j, 64);
-      const float *rec = p.partials + (int64_t(first + i0 + j) * G + hg) * REC + 4 + lane * E;
+  };
+  if (nt <= 4) batches(std::integral_constant<int, 4>{}, 0, 4);
+  else if (nt <= 8) batches(std::integral_constant<int, 8>{}, 0, 8);
+  else batches(std::integral_constant<int, 16>{}, WIDE ? 16 * wave : 0, WIDE ? 16 * kWaves : 16);
+  if (WIDE && nt > 16) {
+    float *st = s_state + wave * (D + 2);
+    if (lane == 0) {
+      st[D] = M;
+      st[D + 1] = L;
+    }
 #pragma unroll
-      for (int e = 0; e < E; ++e) A[e] = fmaf(w, rec[e], A[e]);
+    for (int e = 0; e < E; ++e) st[lane * E + e] = A[e];
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      const float *o = s_state + w * (D + 2);
+      float a2[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) a2[e] = o[lane * E + e];
+      merge_state<E>(M, L, A, o[D], o[D + 1], a2);
     }
   }
   const float inv = L > 0.0f ? 1.0f / L : 0.0f;
@@ -1366,7 +1367,6 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(DecodeParams p, int b
   for (int e = 0; e < E; ++e) A[e] *= inv;
   store_e<ES, E>(static_cast<char *>(p.out) + (int64_t(bh) * D + lane * E) * ES, A);
 }
-
 
 // ---------------------------------------------------------------------------
 // Prefill compactor.
@@ -2301,6 +2301,10 @@ void launch_decode_kernel(const DecodeParams &p, int grid, bool vt, size_t lds, 
 constexpr int64_t kUnitBytes = 256 << 10;
 constexpr int kUnitMaxUnits = 256;
 
+// Heads up to which the combine takes a workgroup each (their waves are all
+// resident at once, and only such layers split units into many pieces).
+constexpr int kWideCombineHeads = 1024;
+
 template <int ES, int D, int G>
 hipError_t decode_impl(const DecodeParams &p, int grid, bool vt, hipStream_t s) {
   const size_t lds = decode_lds_bytes((p.units + p.slot_group - 1) / p.slot_group + 1, G, D,
@@ -2332,10 +2336,15 @@ hipError_t decode_impl(const DecodeParams &p, int grid, bool vt, hipStream_t s) 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int batch = p.units / p.hkv;
-  // one wave per (b, query head); the launch's threads also cover the U units
-  // for the lengths copy (kThreads * blocks >= 64 * batch * hq >= units)
-  const int blocks = (batch * p.hq + kWaves - 1) / kWaves;
-  hipLaunchKernelGGL((combine_kernel<ES, D, G>), dim3(blocks), dim3(kThreads), 0, s, p, batch);
+  // One wave per (b, query head), or on layers with few heads one workgroup; the
+  // launch's threads also cover the U units for the lengths copy (64 threads per
+  // head, heads >= units).
+  const int heads = batch * p.hq;
+  if (heads <= kWideCombineHeads)
+    hipLaunchKernelGGL((combine_kernel<ES, D, G, true>), dim3(heads), dim3(kThreads), 0, s, p, batch);
+  else
+    hipLaunchKernelGGL((combine_kernel<ES, D, G, false>), dim3((heads + kWaves - 1) / kWaves),
+                       dim3(kThreads), 0, s, p, batch);
   return hipGetLastError();
 }
 
