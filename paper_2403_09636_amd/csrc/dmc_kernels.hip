@@ -74,11 +74,17 @@ constexpr int kRangesPerWave = 1;   // slot-space ranges per decode wave (2 and 
 constexpr int kValuUnitOverhead = 32;
 constexpr int kMfmaUnitOverhead = 0;
 // Fewest positions per range: on a short layer, where equal shares would be
-// a few slots, every range still pays its round trips and a partial record.
-constexpr int kMinSpan = 64;
+// a few slots, every range still pays its round trips and a partial record (a
+// chat request's pass of 32 steps: 627 us at 64, 582 at 32).
+constexpr int kMinSpan = 32;
 // Largest excess, in percent of the equal slot share, at which the matrix-core
 // decode gives every wave whole units instead of equal slot ranges.
 constexpr int kWholeUnitSlack = 10;
+// The same for the pieces of one unit per wave that the matrix-core decode
+// prefers on layers with fewer units than waves.
+constexpr int kPieceSlack = 25;
+constexpr int kPieceUnits = 2048;   // most units of such a layer
+static_assert(kMfmaUnitOverhead == 0, "a piece's positions are slots");
 static_assert(kValuUnitOverhead <= kDecodeUnitOverhead && kMfmaUnitOverhead <= kDecodeUnitOverhead,
               "slot-space overhead bound");
 #ifndef DMC_VALU_DECODE_WAVES
@@ -192,37 +198,12 @@ __device__ __forceinline__ void merge_state(float &m, float &l, float *a, float 
 }
 
 
-// Slot space of a layer: unit u owns positions [off_u, off_u + n_u) with
-// n_u = max(l_u, 1) + OVH (pre-step lengths, OVH virtual positions for the
-// piece's fixed cost); position off_u + max(l_u, 1) - 1 is the unit's open
-// slot (or, for an empty unit, the slot its first token opens), and the piece
-// holding the unit's last position owns it.
-// Every workgroup builds the exclusive prefix in LDS and gets S.  The table
-// holds every unit's offset (s_off[0..U]); layers whose full table would not
-// fit in LDS run the GRP kernels, which keep only every g-th entry (g =
-// p.slot_group, a power of two <= 64): s_off[j] = off of unit j g, for
-// j <= NG = ceil(U / g), s_off[NG] = S.
-template <bool GRP, int OVH, int NT = kThreads>
-__device__ __forceinline__ int build_slot_space(const DecodeParams &p, int *s_off, int *s_wsum) {
+// Exclusive prefix of s_off[0 .. n - 1] in place; the total goes to s_off[n] and
+// is returned.  All NT threads of the workgroup take part.
+template <int NT>
+__device__ __forceinline__ int scan_table(int NG, int *s_off, int *s_wsum) {
   constexpr int NW = NT / 64;
-  const int U = p.units, g = GRP ? p.slot_group : 1, NG = (U + g - 1) / g;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kBatch = 8;     // coalesced loads in flight per thread
-  for (int i0 = 0; i0 < U; i0 += NT * kBatch) {
-    int v[kBatch];
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int i = i0 + j * NT + tid;
-      v[j] = i < U ? p.len_in[i] : 0;
-    }
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int i = i0 + j * NT + tid;   // units of a wave are 64 consecutive ones
-      int n = i < U ? max(v[j], 1) + OVH : 0;
-      for (int o = 1; o < g; o <<= 1) n += __shfl_xor(n, o, 64);   // sum over the g-unit group
-      if (i < U && (i & (g - 1)) == 0) s_off[i / g] = n;
-    }
-  }
   __syncthreads();
   const int per = (NG + NT - 1) / NT;
   const int i0 = min(tid * per, NG), i1 = min(i0 + per, NG);
@@ -249,6 +230,58 @@ __device__ __forceinline__ int build_slot_space(const DecodeParams &p, int *s_of
   if (tid == 0) s_off[NG] = total;
   __syncthreads();
   return s_off[NG];
+}
+
+// Slot space of a layer: unit u owns positions [off_u, off_u + n_u) with
+// n_u = max(l_u, 1) + OVH (pre-step lengths, OVH virtual positions for the
+// piece's fixed cost); position off_u + max(l_u, 1) - 1 is the unit's open
+// slot (or, for an empty unit, the slot its first token opens), and the piece
+// holding the unit's last position owns it.
+// Every workgroup builds the exclusive prefix in LDS and gets S.  The table
+// holds every unit's offset (s_off[0..U]); layers whose full table would not
+// fit in LDS run the GRP kernels, which keep only every g-th entry (g =
+// p.slot_group, a power of two <= 64): s_off[j] = off of unit j g, for
+// j <= NG = ceil(U / g), s_off[NG] = S.
+template <bool GRP, int OVH, int NT = kThreads>
+__device__ __forceinline__ int build_slot_space(const DecodeParams &p, int *s_off, int *s_wsum) {
+  const int U = p.units, g = GRP ? p.slot_group : 1, NG = (U + g - 1) / g;
+  const int tid = threadIdx.x;
+  constexpr int kBatch = 8;     // coalesced loads in flight per thread
+  for (int i0 = 0; i0 < U; i0 += NT * kBatch) {
+    int v[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int i = i0 + j * NT + tid;
+      v[j] = i < U ? p.len_in[i] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int i = i0 + j * NT + tid;   // units of a wave are 64 consecutive ones
+      int n = i < U ? max(v[j], 1) + OVH : 0;
+      for (int o = 1; o < g; o <<= 1) n += __shfl_xor(n, o, 64);   // sum over the g-unit group
+      if (i < U && (i & (g - 1)) == 0) s_off[i / g] = n;
+    }
+  }
+  return scan_table<NT>(NG, s_off, s_wsum);
+}
+
+// The slot-space table turned into a piece table: s_off[u] = number of pieces of
+// span positions of the units before u.
+__device__ __forceinline__ void count_pieces(int U, int span, int *s_off, int *s_wsum) {
+  constexpr int kMost = kPieceUnits / kThreads;   // units per thread
+  int n[kMost];
+#pragma unroll
+  for (int j = 0; j < kMost; ++j) {
+    const int u = threadIdx.x + j * kThreads;
+    n[j] = u < U ? (s_off[u + 1] - s_off[u] + span - 1) / span : 0;
+  }
+  __syncthreads();   // every difference is taken
+#pragma unroll
+  for (int j = 0; j < kMost; ++j) {
+    const int u = threadIdx.x + j * kThreads;
+    if (u < U) s_off[u] = n[j];
+  }
+  scan_table<kThreads>(U, s_off, s_wsum);
 }
 
 // Unit holding slot-space position pos (off_u <= pos < off_u + n_u); its
@@ -785,12 +818,61 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
 
   constexpr int OVH = kMfmaUnitOverhead;
   int S = 0, nwaves = 0, span = 1, nranges = 1;
-  bool whole = false;
+  bool whole = false, pieces = false;
   if constexpr (!UNIT) {
     S = build_slot_space<GRP, OVH>(p, s_off, s_wsum);
     nwaves = gridDim.x * kWaves;
     span = max((S + kRangesPerWave * nwaves - 1) / (kRangesPerWave * nwaves), kMinSpan);
     if (p.split_tile > 0 && span > p.split_tile) span = p.split_tile;
+    // Fewer units than waves: pieces of one unit each, if that balances.  Every
+    // unit is cut into pieces of T positions from its start, T the smallest of a
+    // few multiples of 32 from the equal share on (within kPieceSlack) for which
+    // the pieces do not outnumber the waves; then each wave runs one piece of
+    // whole chunks, where an equal range mostly holds the end of one unit and the
+    // start of the next, a second piece start and a chunk streamed twice.  The
+    // table then counts pieces: s_off[u] = first piece of unit u.  70B GQA layer,
+    // 256 units of about 2050 slots: 741 -> 691 us per pass of 8 steps and a
+    // prompt; 104 uneven windowed units of up to 2000: 787 -> 712 us, 24 steps.
+    if constexpr (!GRP) {
+      if (p.split_tile == 0 && U < nwaves && U <= kPieceUnits) {
+        constexpr int kTry = 4;
+        const int t0 = (span + 31) & ~31;
+        int cnt[kTry] = {};
+        for (int u = threadIdx.x; u < U; u += kThreads) {
+          const int n_u = s_off[u + 1] - s_off[u];
+#pragma unroll
+          for (int i = 0; i < kTry; ++i) cnt[i] += (n_u + t0 + 32 * i - 1) / (t0 + 32 * i);
+        }
+#pragma unroll
+        for (int i = 0; i < kTry; ++i) {
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) cnt[i] += __shfl_xor(cnt[i], o, 64);
+        }
+        __shared__ int s_cnt[kWaves][kTry];
+        if (lane == 0) {
+#pragma unroll
+          for (int i = 0; i < kTry; ++i) s_cnt[wave][i] = cnt[i];
+        }
+        __syncthreads();
+        int T = 0;
+#pragma unroll
+        for (int i = kTry - 1; i >= 0; --i) {
+          int c = 0;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) c += s_cnt[w][i];
+          const int t = t0 + 32 * i;
+          if (c <= nwaves && int64_t(t) * 100 <= int64_t(span + 31) * (100 + kPieceSlack)) {
+            T = t;
+            nranges = c;
+          }
+        }
+        if (T > 0) {   // (workgroup-uniform)
+          pieces = true;
+          span = T;
+          count_pieces(U, T, s_off, s_wsum);
+        }
+      }
+    }
     // Whole units when that balances: wave w takes units [w U / W, (w + 1) U / W)
     // in full if no wave's share then exceeds the equal slot share by more than
     // kWholeUnitSlack.  Split units cost this kernel a piece start, an owner
@@ -815,17 +897,19 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         whole = int64_t(mx) * 100 <= int64_t(span) * (100 + kWholeUnitSlack);
       }
     }
-    nranges = whole ? nwaves : (S + span - 1) / span;
+    if (!pieces) nranges = whole ? nwaves : (S + span - 1) / span;
   }
 
   // (few ranges: one per workgroup before the second of any)
   const int r_first = UNIT ? 0 : 2 * nranges <= nwaves ? wave * gridDim.x + blockIdx.x : blockIdx.x * kWaves + wave;
   for (int r = r_first; r < nranges; r += UNIT ? 1 : nwaves) {
     const int wu0 = whole ? static_cast<int>(int64_t(r) * U / nwaves) : 0;
-    int pos = UNIT ? 0 : whole ? s_off[wu0] : r * span;
-    const int pos_end = UNIT    ? 1
-                        : whole ? s_off[static_cast<int>(int64_t(r + 1) * U / nwaves)]
-                                : min(pos + span, S);
+    // positions of the range; pieces count as one position each
+    int pos = UNIT ? 0 : pieces ? r : whole ? s_off[wu0] : r * span;
+    const int pos_end = UNIT     ? 1
+                        : pieces ? r + 1
+                        : whole  ? s_off[static_cast<int>(int64_t(r + 1) * U / nwaves)]
+                                 : min(pos + span, S);
     int off = 0;
     for (int u = UNIT    ? int(blockIdx.x)
                  : whole ? (off = pos, wu0)
@@ -842,6 +926,12 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         end = min(((wave + 1) * chunks / kWaves) << 5, max(l - 1, 0));
         owner = wave == kWaves - 1;
         pos = 1;
+      } else if (!GRP && pieces) {
+        const int n_u = max(l, 1);
+        start = (r - off) * span;
+        owner = start + span >= n_u;
+        end = owner ? n_u - 1 : start + span;
+        pos = pos_end;
       } else {
         if constexpr (!GRP) off = s_off[u];
         const int n_u = GRP ? max(l, 1) + OVH : s_off[u + 1] - off;
@@ -1229,7 +1319,7 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
           if (p.slot_index) p.slot_index[u] = has_cur ? slot : -1;
           if (flag) atomicOr(&p.ctrl->flags, flag);
           if constexpr (!UNIT) {
-            const int r0 = whole ? r : off / span;
+            const int r0 = whole ? r : pieces ? off : off / span;   // the unit's first range
             p.meta[2 * u] = r0 + u;
             p.meta[2 * u + 1] = r - r0 + 1;
           }
