@@ -960,32 +960,54 @@ __global__ __launch_bounds__(64, (tokens_mfma_waves<D, NK>())) void train_tokens
 // prod_{t+1..r-1} alpha; with the mask entry log(1 - alpha_r) of state r - 1
 // and the caller's dalpha they reach the logit x_r, hence k_r[0] (/ tau), and
 // omega reaches q_r[lead][0].
+// A workgroup of blockDim.x tokens stages the weight gradients of its tokens and
+// of the w - 1 before them (rows padded to an odd stride), and their alpha and
+// omega, in LDS: read from global memory, the w (w + 1) / 2 gradients of a token
+// -- each in another row -- took 53 us for 64 units of 4096 tokens (w = 12), now
+// about 25, most of it the 2-byte writes into rows of dk and dq.
+inline int neurons_tokens(int window) { return window <= 32 ? 256 : 128; }
+inline size_t neurons_lds_bytes(int window) {
+  const int tb = neurons_tokens(window);
+  return (size_t(tb + window - 1) * (window | 1) + 2 * size_t(tb + 2 * (window - 1))) * 4;
+}
+
 template <int ES, int D>
 __global__ __launch_bounds__(kThreads) void train_neurons_kernel(TrainParams p) {
-  const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  const int U = p.batch * p.hkv;
-  if (i >= int64_t(U) * p.n) return;
-  const int u = static_cast<int>(i / p.n), r = static_cast<int>(i - int64_t(u) * p.n);
-  const int b = u / p.hkv, g = u - b * p.hkv, G = p.hq / p.hkv, W = p.window;
-  const float *al = p.alpha + int64_t(u) * p.n;
-  const float *om = p.omega + int64_t(u) * p.n;
-  const float *ee = p.e + int64_t(u) * p.n * W;
+  extern __shared__ __align__(16) float s_e[];
+  const int W = p.window, ld = W | 1, tb = blockDim.x;
+  const int u = blockIdx.y, r0 = blockIdx.x * tb, r = r0 + threadIdx.x;
+  const int b = u / p.hkv, g = u - b * p.hkv, G = p.hq / p.hkv;
+  const int64_t un = int64_t(u) * p.n;
+  const int lo = max(0, r0 - W + 1), hi = min(r0 + tb, p.n);   // tokens of the staged rows
+  float *s_al = s_e + (tb + W - 1) * ld, *s_om = s_al + tb + 2 * (W - 1);
+  for (int i = threadIdx.x; i < (hi - lo) * W; i += tb) {
+    const int row = i / W;
+    s_e[row * ld + (i - row * W)] = p.e[(un + lo) * W + i];
+  }
+  for (int t = lo + threadIdx.x; t < min(hi + W - 1, p.n); t += tb) {
+    s_al[t - lo] = p.alpha[un + t];
+    s_om[t - lo] = p.omega[un + t];
+  }
+  __syncthreads();
+  if (r >= p.n) return;
+  auto al = [&](int t) { return s_al[t - lo]; };
+  auto ee = [&](int t, int i) { return s_e[(t - lo) * ld + i]; };   // e of token t in state t + i
   float domega = 0.0f, dalpha = 0.0f, S = 1.0f;
   const int jl = min(r + W - 1, p.n - 1);
   for (int j = r; j <= jl; ++j) {
-    if (j > r) S *= al[j];                   // prod_{r' = r+1 .. j} alpha
-    domega = fmaf(ee[int64_t(r) * W + (j - r)], S, domega);
+    if (j > r) S *= al(j);                   // prod_{r' = r+1 .. j} alpha
+    domega = fmaf(ee(r, j - r), S, domega);
     const int aj = max(0, j - W + 1);
     if (aj < r) {
       float F = 0.0f, Q = 1.0f;
       for (int t = r - 1; t >= aj; --t) {     // Q = prod_{t+1 .. r-1} alpha
-        F = fmaf(ee[int64_t(t) * W + (j - t)] * om[t], Q, F);
-        Q *= al[t];
+        F = fmaf(ee(t, j - t) * s_om[t - lo], Q, F);
+        Q *= al(t);
       }
       dalpha = fmaf(S, F, dalpha);
     }
   }
-  const float a_r = al[r];
+  const float a_r = al(r);
   if (p.dalpha) dalpha += p.dalpha[(int64_t(b) * p.n + r) * p.hkv + g];
   float dx = dalpha * a_r * (1.0f - a_r);
   if (r > 0) dx -= a_r * p.dmask[int64_t(u) * p.n + r - 1];   // d log(1 - sigmoid(x)) / dx = -alpha
@@ -996,7 +1018,7 @@ __global__ __launch_bounds__(kThreads) void train_neurons_kernel(TrainParams p) 
     static_cast<float *>(p.dk)[row_k(p, b, r, g, D)] = dk0;
   }
   if (p.omega_src == 0) {
-    const float w = om[r];
+    const float w = s_om[r - lo];
     const float dq0 = w > 0x1p-100f ? domega * w * (1.0f - w) : 0.0f;
     if constexpr (ES == 2) {
       static_cast<uint16_t *>(p.dq)[row_q(p, b, r, g * G, D)] = static_cast<uint16_t>(bf16_bits(dq0));
@@ -1812,8 +1834,9 @@ hipError_t train_backward_impl(const TrainParams &p, hipStream_t s) {
   } else {
     hipLaunchKernelGGL((train_tokens_kernel<ES, D>), dim3((p.n + 7) / 8, U), dim3(64), 0, s, p);
   }
-  hipLaunchKernelGGL((train_neurons_kernel<ES, D>), dim3(blocks_for(int64_t(U) * p.n)),
-                     dim3(kThreads), 0, s, p);
+  const int tb = neurons_tokens(p.window);
+  hipLaunchKernelGGL((train_neurons_kernel<ES, D>), dim3((p.n + tb - 1) / tb, U), dim3(tb),
+                     neurons_lds_bytes(p.window), s, p);
   return hipGetLastError();
 }
 
