@@ -38,6 +38,17 @@ __device__ __forceinline__ int score_slot(int m) {   // pi(m): bits 2 and 3 swap
   return (m & 0x13) | ((m & 4) << 1) | ((m & 8) >> 1);
 }
 
+// Block row of score register rr of lane half hb, less 8 hb (score_slot of the
+// register's result row: a constant per register, so that masks compare
+// constants with one per-lane value).
+constexpr int score_row(int rr) { return 16 * (rr >> 3) + (rr & 7); }
+// A value kept in one register: the compiler neither splits it per use nor
+// hoists the parts out of a loop (sixteen masks' worth of registers).
+__device__ __forceinline__ int one_register(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 __device__ __forceinline__ uint32_t lds_offset(const void *p) {
   return static_cast<uint32_t>(
       reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char *)p));
@@ -143,6 +154,10 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
+
+// Fixes where a value is computed (it cannot sink past this point, for
+// instance into the branch target where it is used).
+__device__ __forceinline__ void computed_here(float &x) { asm volatile("" : "+v"(x)); }
 
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4_t;

@@ -1272,39 +1272,49 @@ __global__ __launch_bounds__(kThreads, 2) void train_qmajor_kernel(TrainParams p
     const char *kd = reinterpret_cast<const char *>(slot(stage_c));
     const char *vd = kd + BLK;
 
+    // Row operands are read three products ahead (order pinned).
     f32x16_t sc = f32x16_t{};
+    uint4 kr[4];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      sc = mfma_32x32x16(*reinterpret_cast<const uint4 *>(kd + kaddr[ks]), qop[ks], sc);
+    for (int i = 0; i < 3; ++i) kr[i] = *reinterpret_cast<const uint4 *>(kd + kaddr[i]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + 3 < KS) kr[(ks + 3) & 3] = *reinterpret_cast<const uint4 *>(kd + kaddr[ks + 3]);
+      sc = mfma_32x32x16(kr[ks & 3], qop[ks], sc);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    uint4 vr[4];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) vr[i] = *reinterpret_cast<const uint4 *>(vd + kaddr[i]);
     float sv[16];
 #pragma unroll
     for (int rr = 0; rr < 16; ++rr) sv[rr] = sc[rr];
     if (kb * 32 + 32 > a) {   // the block reaches the diagonal
+      const int tr = one_register(t - kb * 32 - 8 * hb);   // (register rr: state kb * 32 + 8 hb + score_row(rr))
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) {
-        const int st = kb * 32 + score_slot(8 * (rr >> 2) + 4 * hb + (rr & 3));
-        if (st > t) sv[rr] = neg_inf();
-        else if (st == t) sv[rr] -= diag;
+        if (score_row(rr) > tr) sv[rr] = neg_inf();
+        else if (score_row(rr) == tr) sv[rr] -= diag;
       }
     }
     {   // dq (the forward runs the pipelined step below)
       // dP^T = V . dO^T, with P = exp2(S - L) (the forward's statistics)
-      // formed between its MFMAs (order pinned; value rows read two ahead),
-      // then dS^T = P^T (dP^T - D).
+      // formed between its MFMAs, and the transposed keys of the last product
+      // read, then dS^T = P^T (dP^T - D).
       f32x16_t dp = f32x16_t{};
       float pe[16];
-      uint4 vr[3];
-      vr[0] = *reinterpret_cast<const uint4 *>(vd + kaddr[0]);
-      vr[1] = *reinterpret_cast<const uint4 *>(vd + kaddr[1]);
+      uint4 kt[NTL][2];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 2 < KS) vr[(ks + 2) % 3] = *reinterpret_cast<const uint4 *>(vd + kaddr[ks + 2]);
-        dp = mfma_32x32x16(vr[ks % 3], dop[ks], dp);
+        if (ks + 3 < KS) vr[(ks + 3) & 3] = *reinterpret_cast<const uint4 *>(vd + kaddr[ks + 3]);
+        dp = mfma_32x32x16(vr[ks & 3], dop[ks], dp);
 #pragma unroll
         for (int e = 0; e < 16 / KS; ++e) {
           const int i = ks * (16 / KS) + e;
           pe[i] = fast_exp2(fmaf(sv[i], sl2, -Lc));
+          computed_here(pe[i]);
         }
+        kt[ks >> 1][ks & 1] = tr_operand<RB>(kd, traddr[ks >> 1], ks & 1);
         __builtin_amdgcn_sched_barrier(0);
       }
       uint4 sb[2];
@@ -1322,7 +1332,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_qmajor_kernel(TrainParams p
       for (int i = 0; i < NTL; ++i)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
-          acc[i] = mfma_32x32x16(tr_operand<RB>(kd, traddr[i], kk), sb[kk], acc[i]);
+          acc[i] = mfma_32x32x16(kt[i][kk], sb[kk], acc[i]);
     }
   };
 
@@ -1352,15 +1362,21 @@ __global__ __launch_bounds__(kThreads, 2) void train_qmajor_kernel(TrainParams p
       if (kb * 32 >= wave_hi) return;
       const char *vd = reinterpret_cast<const char *>(slot(stage_c)) + BLK;
       const char *kn = reinterpret_cast<const char *>(slot(std::integral_constant<int, SN>{}));   // block kb + 1's keys
+      // The next block's slot always holds readable data; past the last
+      // block its scores are not used.  Key operands are read three products
+      // ahead, the value operands during the score products.
+      uint4 kr[4], va[NTL][2];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) kr[i] = *reinterpret_cast<const uint4 *>(kn + kaddr[i]);
       float sv[16];
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) sv[rr] = scn[rr];
       if (kb * 32 + 32 > a) {   // the block reaches the diagonal
+        const int tr = one_register(t - kb * 32 - 8 * hb);
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) {
-          const int st = kb * 32 + score_slot(8 * (rr >> 2) + 4 * hb + (rr & 3));
-          if (st > t) sv[rr] = neg_inf();
-          else if (st == t) sv[rr] -= diag;
+          if (score_row(rr) > tr) sv[rr] = neg_inf();
+          else if (score_row(rr) == tr) sv[rr] -= diag;
         }
       }
       float mx = fmaxf(fmaxf(sv[0], sv[1]), sv[2]);
@@ -1376,22 +1392,20 @@ __global__ __launch_bounds__(kThreads, 2) void train_qmajor_kernel(TrainParams p
 #pragma unroll
         for (int i = 0; i < NTL; ++i) acc[i] *= f;
       }
-      // The next block's slot always holds readable data; past the last
-      // block its scores are not used.
-      uint4 kr[3];
-      kr[0] = *reinterpret_cast<const uint4 *>(kn + kaddr[0]);
-      kr[1] = *reinterpret_cast<const uint4 *>(kn + kaddr[1]);
       f32x16_t sc = f32x16_t{};
       float ev[16];
+      static_assert(KS == 2 * NTL && KS > 3, "one value operand per score product");
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 2 < KS) kr[(ks + 2) % 3] = *reinterpret_cast<const uint4 *>(kn + kaddr[ks + 2]);
-        sc = mfma_32x32x16(kr[ks % 3], qop[ks], sc);
+        if (ks + 3 < KS) kr[(ks + 3) & 3] = *reinterpret_cast<const uint4 *>(kn + kaddr[ks + 3]);
+        sc = mfma_32x32x16(kr[ks & 3], qop[ks], sc);
 #pragma unroll
         for (int e = 0; e < 16 / KS; ++e) {
           const int i = ks * (16 / KS) + e;
           ev[i] = fast_exp2(fmaf(sv[i], sl2, -m));
+          computed_here(ev[i]);
         }
+        va[ks >> 1][ks & 1] = tr_operand<RB>(vd, traddr[ks >> 1], ks & 1);
         __builtin_amdgcn_sched_barrier(0);
       }
       scn = sc;
@@ -1410,7 +1424,7 @@ __global__ __launch_bounds__(kThreads, 2) void train_qmajor_kernel(TrainParams p
       for (int i = 0; i < NTL; ++i)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
-          acc[i] = mfma_32x32x16(tr_operand<RB>(vd, traddr[i], kk), pb[kk], acc[i]);
+          acc[i] = mfma_32x32x16(va[i][kk], pb[kk], acc[i]);
     };
     // Whole rounds of four steps (a step past the last block only keeps the
     // barriers and transfer counts in step).
@@ -1584,6 +1598,8 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_mfma_kernel(TrainParams
     const char *qd = reinterpret_cast<const char *>(slot(stage_c));
     const char *dd = qd + BLK;
     const bool interior = rb / G > s0 + 31 && rb + 32 <= nrows && s0 + 32 <= p.n;
+    // this lane's state and the end of the rows, against a register's constant row
+    const int js_rel = one_register(js - rb / G - hb * (8 / G)), rows_rel = one_register(nrows - rb - 8 * hb);
     f32x16_t sc = f32x16_t{}, dp = f32x16_t{};
     // Softmax statistics of register 8 kk + q of this lane: row rb + 16 kk +
     // 8 hb + q (pi-permuted rows), from this wave's copy of the block's
@@ -1692,13 +1708,13 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_mfma_kernel(TrainParams
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             const int i = 8 * kk + 2 * q + e;
-            const int rg = rb + 16 * kk + 8 * hb + 2 * q + e;
-            const int tq = rg / G;
-            const bool vis = sv_ok && rg < nrows && tq >= js;
-            const float x = sc[i] * sl2 - (tq > js ? 0.0f : bias);   // no bias on the diagonal
+            const int rel = 16 * kk + 2 * q + e;   // the block row less 8 hb: token rel / G, less 8 hb / G
+            const bool past = rel / G > js_rel;
+            const bool vis = sv_ok && rel < rows_rel && rel / G >= js_rel;
+            const float x = sc[i] * sl2 - (past ? 0.0f : bias);   // no bias on the diagonal
             pv[e] = vis ? fast_exp2(x - Lr[i]) : 0.0f;
             dsv[e] = vis ? pv[e] * (dp[i] - Dr[i]) : 0.0f;   // statistics past the rows are not read
-            if (vis && tq > js) dm += dsv[e];
+            if (vis && past) dm += dsv[e];
           }
           wp[q] = cvt_pk_bf16(pv[0], pv[1]);
           wd[q] = cvt_pk_bf16(dsv[0], dsv[1]);
