@@ -236,23 +236,18 @@ dmc_status check_layer(const dmc_cache *c, int32_t layer) {
 }
 
 dmc_status enqueue_reset(dmc_cache *c, hipStream_t s) {
-  const size_t U = c->lay.units, NL = c->cfg.num_layers;
-  hipError_t e;
-  if ((e = dmc::launch_fill_i32(at<int32_t>(c, c->lay.lens), 0, 2 * NL * U, s)) != hipSuccess)
-    return hip_fail(e, "reset lengths");
-  if ((e = dmc::launch_fill_i32(at<int32_t>(c, c->lay.z), 0, NL * U, s)) != hipSuccess)
-    return hip_fail(e, "reset z");
-  if ((e = dmc::launch_fill_i32(at<int32_t>(c, c->lay.ptab), -1, NL * U * c->lay.maxpages, s)) !=
-      hipSuccess)
-    return hip_fail(e, "reset page table");
-  if ((e = dmc::launch_fill_u8(c->ws + c->lay.ctrl, sizeof(dmc::Control), s)) != hipSuccess)
-    return hip_fail(e, "reset control block");
-  if ((e = dmc::launch_fill_i32(at<int32_t>(c, c->lay.meta), 0, 2 * U, s)) != hipSuccess)
-    return hip_fail(e, "reset tile table");
-  if (c->lay.window > 0 &&
-      (e = dmc::launch_fill_i32(at<int32_t>(c, c->lay.win_len), 0, NL * U, s)) != hipSuccess)
-    return hip_fail(e, "reset window lengths");
-  return DMC_OK;
+  dmc::ResetParams p{};
+  p.units = c->lay.units;
+  p.all_units = p.units * c->cfg.num_layers;
+  p.table = p.all_units * c->lay.maxpages;
+  p.ptab = at<int32_t>(c, c->lay.ptab);
+  p.lens = at<int32_t>(c, c->lay.lens);
+  p.z = at<float>(c, c->lay.z);
+  p.ctrl = at<dmc::Control>(c, c->lay.ctrl);
+  p.meta = at<int32_t>(c, c->lay.meta);
+  p.win_len = c->lay.window > 0 ? at<int32_t>(c, c->lay.win_len) : nullptr;
+  const hipError_t e = dmc::launch_reset(p, s);
+  return e == hipSuccess ? DMC_OK : hip_fail(e, "reset");
 }
 
 }  // namespace

@@ -131,6 +131,18 @@ struct PromptParams {
   int32_t window;          // window grouping: open states over the last `window` tokens
 };
 
+// What a reset clears: page tables (-1), lengths (two buffers), z, the control
+// block, the record table and the windows' segment lengths (0).
+struct ResetParams {
+  int32_t *ptab;
+  int32_t *lens;
+  float *z;
+  Control *ctrl;
+  int32_t *meta;
+  int32_t *win_len;        // null without a window
+  size_t table, all_units, units;   // page-table entries, units of all layers, of one layer
+};
+
 struct DenseParams {
   char *pool;
   int64_t page_bytes;
@@ -187,7 +199,7 @@ hipError_t launch_train_backward(int elem_bytes, int head_dim, int group, const 
                                  hipStream_t s);
 
 // Launchers (return hipGetLastError() after enqueueing).
-hipError_t launch_fill_i32(int32_t *p, int32_t value, size_t count, hipStream_t s);
+hipError_t launch_reset(const ResetParams &p, hipStream_t s);
 hipError_t launch_fill_u8(void *p, size_t bytes, hipStream_t s);
 hipError_t launch_copy_i32(int32_t *dst, const int32_t *src, size_t count, hipStream_t s);
 // vt: value pages stored transposed ([d][32] per page; bf16, G >= 4, P == 32),
