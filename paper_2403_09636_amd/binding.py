@@ -205,6 +205,47 @@ def check_decode_args(cfg, device, q, k, v, out, slot_index=None):
     _on_device(device, q=q, k=k, v=v, out=out, slot_index=slot_index)
 
 
+class _DecodeCall:
+    """The tensor checks of a decode step in one pass, for steps whose GPU time
+    is a few microseconds: the same conditions as check_decode_args, tested on
+    every call against the configuration's dtype and shapes, without a message.
+    pointers() returns the addresses of q, k, v, out and slot_index, or None if
+    any condition fails (check_decode_args then names it)."""
+
+    def __init__(self, cfg, device):
+        import torch
+        self.Tensor = torch.Tensor
+        self.device, self.dtype, self.i32 = device, cache_dtype(cfg), torch.int32
+        self.q_shape = (cfg.batch, cfg.num_q_heads, cfg.head_dim)
+        self.kv_shape = (cfg.batch, cfg.num_kv_heads, cfg.head_dim)
+        self.slot_shape = (cfg.batch, cfg.num_kv_heads)
+        es = 4 if cfg.dtype == DMC_FP32 else 2
+        self.q_bytes = cfg.batch * cfg.num_q_heads * cfg.head_dim * es
+        self.kv_bytes = cfg.batch * cfg.num_kv_heads * cfg.head_dim * es
+
+    def pointers(self, q, k, v, out, slot_index):
+        device, dtype, tensor = self.device, self.dtype, self.Tensor
+        for t, shape in ((q, self.q_shape), (k, self.kv_shape), (v, self.kv_shape), (out, self.q_shape)):
+            if not (isinstance(t, tensor) and t.dtype is dtype and t.shape == shape
+                    and t.is_contiguous() and t.device == device):
+                return None
+        sp = None
+        if slot_index is not None:
+            if not (isinstance(slot_index, tensor) and slot_index.dtype is self.i32
+                    and slot_index.shape == self.slot_shape and slot_index.is_contiguous()
+                    and slot_index.device == device):
+                return None
+            sp = slot_index.data_ptr()
+        qp, kp, vp, op = q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr()
+        if (qp | kp | vp | op) & 15:
+            return None
+        end = op + self.q_bytes
+        if ((op < qp + self.q_bytes and qp < end) or (op < kp + self.kv_bytes and kp < end)
+                or (op < vp + self.kv_bytes and vp < end)):
+            return None
+        return qp, kp, vp, op, sp
+
+
 def _overlap(x, y):
     if x.numel() == 0 or y.numel() == 0:
         return False
@@ -291,8 +332,10 @@ def check_train_args(cfg, device, q, k, v, noise, extra=()):
 
 def _stream(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # no Stream object around the handle
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def _cuda_device(device):
@@ -327,6 +370,7 @@ class DMCCache:
         check(lib.dmc_cache_alloc(ctypes.byref(cfg), c_void_p(self._ws_ptr), nbytes,
                                   _stream(stream), ctypes.byref(handle)))
         self.handle = handle
+        self._decode_call = _DecodeCall(cfg, self.device)
 
     def close(self):
         if getattr(self, "handle", None):
@@ -340,22 +384,25 @@ class DMCCache:
             pass
 
     # -- hot path -------------------------------------------------------------
+    def _decode(self, step, layer, q, k, v, out, slot_index, stream):
+        ptrs = self._decode_call.pointers(q, k, v, out, slot_index)
+        if ptrs is None:
+            check_decode_args(self.cfg, self.device, q, k, v, out, slot_index)
+            ptrs = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+                    None if slot_index is None else slot_index.data_ptr())
+        check(step(self.handle, layer, *ptrs, _stream(stream)))
+        return out
+
     def decode_step(self, layer, q, k, v, out=None, slot_index=None, stream=None):
         """Algorithm 1 update + attention for one layer; returns out [B, Hq, d]."""
         if out is None:
             out = torch_empty_like(q)
-        check_decode_args(self.cfg, self.device, q, k, v, out, slot_index)
-        check(lib.dmc_decode_step(self.handle, layer, _ptr(q), _ptr(k), _ptr(v), _ptr(out),
-                                  _ptr(slot_index), _stream(stream)))
-        return out
+        return self._decode(lib.dmc_decode_step, layer, q, k, v, out, slot_index, stream)
 
     def decode_step_static(self, layer, q, k, v, out, slot_index=None, stream=None):
         """dmc_decode_step_static: as decode_step, with the split-K records in the
         library's static device scratch; allocates nothing (`out` is required)."""
-        check_decode_args(self.cfg, self.device, q, k, v, out, slot_index)
-        check(lib.dmc_decode_step_static(self.handle, layer, _ptr(q), _ptr(k), _ptr(v),
-                                         _ptr(out), _ptr(slot_index), _stream(stream)))
-        return out
+        return self._decode(lib.dmc_decode_step_static, layer, q, k, v, out, slot_index, stream)
 
     def prefill(self, layer, k, v, q, n=None, prompt_lens=None, slot_index=None, stream=None):
         """Compress a prompt: k, v [B, n, Hkv, d] (strided), q [B, n, Hq, (d)]."""
