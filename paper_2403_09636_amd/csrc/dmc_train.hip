@@ -964,7 +964,7 @@ __global__ __launch_bounds__(64, (tokens_mfma_waves<D, NK>())) void train_tokens
 // of the w - 1 before them (rows padded to an odd stride), and their alpha and
 // omega, in LDS: read from global memory, the w (w + 1) / 2 gradients of a token
 // -- each in another row -- took 53 us for 64 units of 4096 tokens (w = 12), now
-// about 25, most of it the 2-byte writes into rows of dk and dq.
+// 29, most of it the 2-byte writes into rows of dk and dq.
 inline int neurons_tokens(int window) { return window <= 32 ? 256 : 128; }
 inline size_t neurons_lds_bytes(int window) {
   const int tb = neurons_tokens(window);
