@@ -2406,7 +2406,17 @@ void launch_decode_kernel(const DecodeParams &p, int grid, bool vt, size_t lds, 
 // what the slot-space table and the combine launch of the general path cost; and
 // up to 256 units the workgroups are all resident at once, one per compute unit.
 // Four fp32 units of up to 64 slots: 5.3 + 7.8 (combine) -> 3.8 us per step.
-constexpr int64_t kUnitBytes = 256 << 10;
+// On the matrix cores the general path costs more (it copies each chunk of a
+// piece through its ring before the first product), so from kUnitWideUnits units,
+// which keep enough memory requests in flight, 512 KB are still faster.  A pass
+// of prefill and 16 steps at 1000 tokens, two layouts of 4 and 8 query heads per
+// kv head: 64 units 357 -> 322 us, 128 421 -> 380, 256 545 -> 462 (700 tokens:
+// 472 -> 378); 32 units would go from 343 to 360 and 8 from 305 to 339.
+template <int ES, int G>
+constexpr int64_t unit_bytes(int units) {
+  constexpr int kUnitBytes = 256 << 10, kUnitWideUnits = 64;
+  return ES == 2 && G >= 4 && units >= kUnitWideUnits ? 2 * kUnitBytes : kUnitBytes;
+}
 constexpr int kUnitMaxUnits = 256;
 
 // Heads up to which the combine takes a workgroup each (their waves are all
@@ -2419,7 +2429,8 @@ hipError_t decode_impl(const DecodeParams &p, int grid, bool vt, hipStream_t s) 
                                       p.win.window > 0);
   if (vt && !(ES == 2 && G >= 4)) return hipErrorInvalidValue;
   // Short caches: one workgroup per unit, one launch per step.
-  if (p.split_tile == 0 && p.units <= kUnitMaxUnits && int64_t(p.max_slots) * 2 * D * ES <= kUnitBytes) {
+  if (p.split_tile == 0 && p.units <= kUnitMaxUnits &&
+      int64_t(p.max_slots) * 2 * D * ES <= unit_bytes<ES, G>(p.units)) {
     const size_t unit_lds = decode_lds_bytes(0, G, D, p.win.window > 0);
     if (p.win.window > 0)
       launch_decode_kernel<ES, D, G, true, false, true>(p, p.units, vt, unit_lds, s);

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
     ("fp32", 64, 1, 32, 260), ("fp32", 128, 8, 8, 130), ("bf16", 128, 1, 32, 512),
     ("bf16", 64, 2, 16, 300), ("bf16", 128, 8, 32, 259), ("bf16", 64, 4, 32, 1024),
     ("bf16", 128, 4, 64, 200),
+    ("bf16", 128, 8, 32, 1000), ("bf16", 128, 4, 32, 1024),   # (80 units: the wider limit)
 ])
 def test_unit_decode_matches_general(torch_cuda, dtype, d, G, page, cap):
     import torch
@@ -21,6 +22,7 @@ def test_unit_decode_matches_general(torch_cuda, dtype, d, G, page, cap):
     lens = [0, 1, 2, 16, 17, 18, 31, 32, 33, 34, 64, 65, 66, 100, 127, 128, 129, cap - 2, cap - 1, cap]
     lens = [x for x in lens if x <= cap]
     lens += [cap // 2] * (-len(lens) % Hkv)
+    lens *= 4 if cap * d > 1 << 16 else 1
     B = len(lens) // Hkv
     gen = torch.Generator().manual_seed(cap)
 
