@@ -64,7 +64,7 @@ struct DecodeParams {
   int64_t num_pages;
   int32_t *ptab;           // [U, maxpages] of this layer
   int32_t *len_in;         // [U] lengths before this step (the layer's current lengths)
-  int32_t *len_out;        // [U] lengths after this step; the combine launch copies them
+  int32_t *len_out;        // [U] lengths after this step (one-launch steps write len_in); the combine launch copies them
                            // back into len_in
   float *z;                // [U]
   Control *ctrl;
@@ -225,8 +225,8 @@ constexpr int kMaxWindow = 64;
 // (its page-table slice is held in LDS).
 constexpr int kPromptMaxPages = 1024;
 
-// Prompt-phase attention; bf16 runs on matrix cores (value pages read as rows,
-// or as the transposed pages of grouped-query caches), fp32 on the vector ALUs.
+// Prompt-phase attention on the matrix cores; bf16 reads value pages as rows or as
+// the transposed pages of grouped-query caches, fp32 as rows.
 hipError_t launch_prompt_attend(int elem_bytes, int head_dim, int group, bool vt,
                                 const PromptParams &p, const Control *ctrl, hipStream_t s);
 

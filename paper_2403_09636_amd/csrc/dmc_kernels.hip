@@ -17,7 +17,9 @@
 //
 // Decode = one fused launch per layer (Algorithm 1 update + split-K
 // attention, balanced by actual compressed length) plus a small combine
-// launch for units split over several pieces.
+// launch for units split over several pieces.  Short caches (unit_bytes) run
+// the fused launch alone, one workgroup per unit, and its owners write their
+// lengths to buffer 0 (no other workgroup reads them).
 #include "dmc_device.h"
 #include "dmc_mfma.h"
 
@@ -1362,8 +1364,8 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
 // batches of 16.  Short and uneven layers split their long units into tens of
 // pieces; they have few heads, so there (WIDE) a workgroup's four waves share a
 // head's batches and merge in LDS.  One chat request (32 heads, up to 60 records
-// before ranges had a least size, 17 since): 13.3 -> 4.8 us per launch; 240
-// uneven heads, up to 61 records: about 7.9 -> 4.4 us.  The launch also copies the
+// before ranges had a least size of 32 slots): 13.3 -> 4.2 us per launch; 240
+// uneven heads, up to 61 records: 7.9 -> 4.8 us.  The launch also copies the
 // step's post-update lengths back into the layer's current-lengths buffer
 // (every unit's owner wrote len_out; this launch runs after all of them).
 template <int ES, int D, int G, bool WIDE>
