@@ -759,8 +759,16 @@ __device__ __forceinline__ float window_mean_lds(const DecodeParams &p, int u, i
 // the 8 consecutive rows 8q..8q+7 of one head -- exactly its slice of the
 // P^T operand of the value product.  Value pages of such caches are stored
 // transposed (V^T: d rows of page_size slots) so that slice of V^T is one
-// 16-byte load.  P enters the value product rounded to bf16; its row sum is
-// taken over the same rounded values.
+// 16-byte load.
+//
+// P enters the value product as two bf16 terms: columns G .. 2G - 1 of the
+// 16-wide operand, which G <= 8 heads leave idle, repeat the heads, and their
+// lanes put in what the leading bf16 bits of P (the heads' own columns) leave
+// off.  The two columns of a head are added once per piece.  Rounded to one
+// bf16 term, P's error against a piece's running maximum was half of the
+// output's (relative 2-norm error against 64 bits 0.0022, where rounding the
+// output alone gives 0.0017) and moved with the places where units are cut;
+// with two it is 2^-16 of P and the products cost the same.
 //
 // Chunks stream through LDS: each wave owns two chunk-sized LDS slots (keys,
 // then V^T), filled by direct global-to-LDS transfers.  The wave copies a
@@ -814,6 +822,7 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
   __shared__ __align__(16) float s_state[UNIT ? kWaves * G * REC : 4];     // the waves' states (UNIT)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, q = lane >> 4;      // MFMA column (head or dim) and k-group
+  const int hn = n & (G - 1);                  // the column's head
   const int P = 1 << p.log2p;
   const int krow = 8 * (n >> 2) + (n & 3);     // this lane's key row in score tile 0 (+4 in tile 1)
   const uint4 zero4 = make_uint4(0, 0, 0, 0);
@@ -946,13 +955,12 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
       const int b = u / p.hkv, g = u - b * p.hkv;
       const int64_t pt = int64_t(u) * p.maxpages;
 
-      // Q^T operand: lane (n, q) holds Q[head n][32 ks + 8q .. +8]; heads >= G are 0.
+      // Q^T operand: lane (n, q) holds Q[head n % G][32 ks + 8q .. +8].
       uint4 qb[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        qb[ks] = n < G ? ld16(static_cast<const char *>(p.q) +
-                              (int64_t(b * p.hq + g * G + n) * D + ks * 32 + 8 * q) * 2)
-                       : zero4;
+        qb[ks] = ld16(static_cast<const char *>(p.q) +
+                      (int64_t(b * p.hq + g * G + hn) * D + ks * 32 + 8 * q) * 2);
       if (q == 0) qb[0].x &= 0xffff0000u;              // Algorithm 1: q_t[0] <- 0
 
       float m = neg_inf(), ls = 0.0f;
@@ -991,11 +999,17 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[nt] *= f;
         m = mn;
+        // Leading bits (truncated) and the rest, which is kept positive so that an
+        // infinite value stays one (2^-100 of a finite one is lost in the sum).
         uint32_t pw[4];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          pw[w] = bf16_pair(fast_exp2(sv[2 * w] - mn), fast_exp2(sv[2 * w + 1] - mn));
-          ls += __uint_as_float(pw[w] << 16) + __uint_as_float(pw[w] & 0xffff0000u);
+          const float p0 = fast_exp2(sv[2 * w] - mn), p1 = fast_exp2(sv[2 * w + 1] - mn);
+          const uint32_t h0 = __float_as_uint(p0) & 0xffff0000u, h1 = __float_as_uint(p1) & 0xffff0000u;
+          const uint32_t rest = cvt_pk_bf16(fmaxf(p0 - __uint_as_float(h0), 0x1p-100f),
+                                            fmaxf(p1 - __uint_as_float(h1), 0x1p-100f));
+          pw[w] = (n & G) ? rest : (h0 >> 16) | h1;
+          ls += p0 + p1;
         }
         const uint4 pb = make_uint4(pw[0], pw[1], pw[2], pw[3]);
         // Rows past the unit's length hold unwritten page memory: clear them in V^T.
@@ -1012,6 +1026,20 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
           va[nt].w &= keep[3];
           acc[nt] = mfma_16x16x32(va[nt], pb, acc[nt]);
         }
+      };
+
+      // Adds the second terms' columns to the heads' (lane n <- n + G of its row of 16)
+      // and clears them.
+      auto fold_columns = [&]() {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float x = acc[nt][i];
+            const float second = __builtin_bit_cast(
+                float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x100 + G, 0xF, 0xF, true));
+            acc[nt][i] = n < G ? x + second : 0.0f;
+          }
       };
 
       // Owner inputs are issued before the stream so that they arrive while it runs:
@@ -1138,6 +1166,7 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
       }
 
       if constexpr (UNIT) {   // the waves' states meet in the owner
+        fold_columns();
         if (!owner) {
           ls += __shfl_xor(ls, 16, 64);
           ls += __shfl_xor(ls, 32, 64);
@@ -1157,15 +1186,15 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         if (!owner) return;
 #pragma unroll 1
         for (int w = 0; w < kWaves - 1; ++w) {
-          const float *rec = s_state + (w * G + (n < G ? n : 0)) * REC;
+          const float *rec = s_state + (w * G + hn) * REC;
           const float m2 = rec[0], mn = fmaxf(m, m2);
-          if (n < G && mn != neg_inf()) {   // (the record's sum counted in one of the column's four lanes)
+          if (mn != neg_inf()) {   // (the record's sum counted in one of the column's four lanes)
             const float f1 = fast_exp2(m - mn), f2 = fast_exp2(m2 - mn);
             ls = ls * f1 + (q == 0 ? rec[1] * f2 : 0.0f);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
               const float4 x = *reinterpret_cast<const float4 *>(rec + 4 + 16 * nt + 4 * q);
-              acc[nt] = acc[nt] * f1 + f32x4_t{x.x, x.y, x.z, x.w} * f2;
+              if (n < G) acc[nt] = acc[nt] * f1 + f32x4_t{x.x, x.y, x.z, x.w} * f2;
             }
             m = mn;
           }
@@ -1328,6 +1357,7 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         }
       }
 
+      fold_columns();
       ls += __shfl_xor(ls, 16, 64);
       ls += __shfl_xor(ls, 32, 64);
       if (n < G) {
