@@ -570,6 +570,10 @@ __global__ __launch_bounds__(kThreads) void train_dkv_f32_kernel(TrainParams p, 
     F::load_row(qr, static_cast<const float *>(p.q) + row_at(qb * 32 + col), hb);
     if (hb == 0) qr[0][0] = 0.0f;   // q[0] is not part of the score
   };
+  // Blocks with rows that some column does not see: tokens before its state, or the copies
+  // of the last row that fill the last block.
+  const unsigned unmasked = max((nrows >> 5) - (qb0 + G), 0);
+  auto masked = [&](int qb) { return unsigned(qb - (qb0 + G)) >= unmasked; };
   load_q(qb0 + wave);
   bool out_v = false, out_k = false;
 #pragma unroll 1
@@ -603,12 +607,12 @@ __global__ __launch_bounds__(kThreads) void train_dkv_f32_kernel(TrainParams p, 
         if (tq > js) dm += ds[r];
       }
     }
-    const bool masked = qb < qb0 + G;   // tokens before some column's state
-    if constexpr (DV) out_v |= F::template add_rows<true>(dv, oc, do_row, pv, lane, masked);
-    if constexpr (DK) out_k |= F::template add_rows<true>(dk, qc, q_row, ds, lane, masked);
+    if constexpr (DV) out_v |= F::template add_rows<true>(dv, oc, do_row, pv, lane, masked(qb));
+    if constexpr (DK) out_k |= F::template add_rows<true>(dk, qc, q_row, ds, lane, masked(qb));
   }
   if (__any(out_v || out_k)) {
-    for (int qb = qb0 + wave; qb < min(qb0 + G, qb1); qb += kWaves) {
+    for (int qb = qb0 + wave; qb < qb1; qb += kWaves) {
+      if (!masked(qb)) continue;
       auto sees = [&](int i) { return qb * 32 + i < nrows && (qb * 32 + i) / G >= js; };
       if constexpr (DV)
         F::add_nonfinite(dv, [&](int i) { return static_cast<const float *>(p.dout) + row_at(qb * 32 + i); },

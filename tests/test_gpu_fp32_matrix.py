@@ -55,6 +55,27 @@ def test_train_nonfinite_rows(torch_cuda, d, G):
     assert torch.isnan(dv[0, r]).any()
 
 
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4)])
+def test_train_infinite_last_row(torch_cuda, d, G):
+    """An infinite gradient element of the last token reaches every token's dV as an
+    infinity: the last block's padding (n G no multiple of 32) adds nothing."""
+    import torch
+    import paper_2403_09636_amd as P
+    log(f"case infinite last row d={d} G={G}")
+    n, w = 109, 4
+    gen = torch.Generator().manual_seed(17 + d)
+    q, k, v, dout = (torch.randn((1, n, h, d), generator=gen).cuda() for h in (G, 1, 1, G))
+    dout[0, n - 1, 0, 3], dout[0, n - 1, G - 1, 6] = float("inf"), -float("inf")
+    noise = torch.zeros((1, n, 1), device="cuda")
+    tr = P.DMCTrainer(P.make_train_config(1, n, G, 1, d, "fp32", decision_bias=0.0, temperature=1.0,
+                                          window=w))
+    out = tr.forward(q, k, v, noise)
+    dv = tr.backward(q, k, v, noise, out, dout)[2][0, :, 0]
+    assert (dv[:, 3] == float("inf")).all() and (dv[:, 6] == -float("inf")).all()
+    rest = [e for e in range(d) if e not in (3, 6)]
+    assert torch.isfinite(dv[:, rest]).all()
+
+
 @pytest.mark.parametrize("d,G,w", [(64, 2, 0), (128, 1, 0), (128, 4, 5)])
 def test_prompt_nonfinite_rows(torch_cuda, d, G, w):
     import torch
