@@ -12,6 +12,7 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_huge_valf(); }
+__device__ __forceinline__ float lowest() { return -3.402823466e38f; }   // finite
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }

@@ -776,7 +776,8 @@ __global__ __launch_bounds__(kThreads) void prompt_f32_kernel(PromptParams p, in
   __syncthreads();
   const float *qs = F::staged(s_acc, lane);
 
-  float m = -1e30f, ls = 0.0f;
+  // (the lowest finite value: a wave that has seen nothing must not outweigh any score)
+  float m = lowest(), ls = 0.0f;
   f32x16_t acc[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) acc[i] = f32x16_t{};
@@ -851,6 +852,7 @@ __global__ __launch_bounds__(kThreads) void prompt_f32_kernel(PromptParams p, in
     const float inv = colv ? 1.0f / zs : 0.0f;
     if (colv) {
       m = part * inv * p.scale_log2;
+      if (m == neg_inf()) m = lowest();   // (by itself it still has weight 1)
       ls = hb == 0 ? 1.0f : 0.0f;   // the open state's weight, counted once per column
     }
 #pragma unroll

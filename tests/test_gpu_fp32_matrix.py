@@ -100,3 +100,30 @@ def test_prompt_nonfinite_rows(torch_cuda, d, G, w):
     assert torch.isfinite(out[0, :s]).all()
     torch.testing.assert_close(out[0, :s], ref[0, :s], rtol=1e-4, atol=1e-5)
     assert torch.isnan(out[0, s:, :, 5]).all()
+
+
+def _low_scores(d, Hq, Hkv, n, size):
+    """Every score of every query is -size^2 / sqrt(d), and the softmax uniform (size a power
+    of two: scaled scores are exact, where a rounding of 2^80 would decide the softmax)."""
+    import torch
+    q, k = torch.zeros((1, n, Hq, d)), torch.zeros((1, n, Hkv, d))
+    q[..., 1], k[..., 1], k[..., 0] = size, -size, -9.0   # (every token opens a slot)
+    v = torch.randn((1, n, Hkv, d), generator=torch.Generator().manual_seed(d))
+    mean = v.double().cumsum(1) / torch.arange(1, n + 1)[None, :, None, None]
+    return q.cuda(), k.cuda(), v.cuda(), mean.repeat_interleave(Hq // Hkv, 2)
+
+
+@pytest.mark.parametrize("d,G,w", [(64, 1, 0), (128, 4, 0), (64, 8, 5)])
+def test_prompt_lowest_scores(torch_cuda, d, G, w):
+    """Scores far below -1e30 still make a softmax; one of -infinity by itself is the token's own."""
+    import torch
+    import paper_2403_09636_amd as P
+    log(f"case prompt lowest scores d={d} G={G} w={w}")
+    n = 150
+    cache = P.DMCCache(P.make_config(1, 1, 2 * G, 2, d, "fp32", max_slots_per_seq=n, omega_src="uniform",
+                                     window=w))
+    for size, upto in ((2.0 ** 57, n), (2.0 ** 83, 1)):
+        q, k, v, mean = _low_scores(d, 2 * G, 2, n, size)
+        cache.reset()
+        out = cache.prefill_attend(0, k, v, q).cpu().double()
+        torch.testing.assert_close(out[:, :upto], mean[:, :upto], rtol=1e-5, atol=1e-5)
