@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kThreads) void train_fwd_f32_kernel(TrainParams p, 
   __syncthreads();
   const float *qs = F::staged(s_acc, lane);
   typename F::f4_t kr[F::NJ];
-  float m = -1e30f, ls = 0.0f;
+  float m = lowest(), ls = 0.0f;
   f32x16_t acc[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) acc[i] = f32x16_t{};

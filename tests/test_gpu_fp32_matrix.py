@@ -127,3 +127,17 @@ def test_prompt_lowest_scores(torch_cuda, d, G, w):
         cache.reset()
         out = cache.prefill_attend(0, k, v, q).cpu().double()
         torch.testing.assert_close(out[:, :upto], mean[:, :upto], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4), (64, 8)])
+def test_train_lowest_scores(torch_cuda, d, G):
+    import torch
+    import paper_2403_09636_amd as P
+    log(f"case train lowest scores d={d} G={G}")
+    n = 109
+    q, k, v, mean = _low_scores(d, 2 * G, 2, n, 2.0 ** 57)
+    tr = P.DMCTrainer(P.make_train_config(1, n, 2 * G, 2, d, "fp32", decision_bias=0.0, temperature=1.0,
+                                          window=1, omega_src="uniform"))
+    out = tr.forward(q, k, v, torch.zeros((1, n, 2), device="cuda")).cpu().double()
+    # (the mask entries are lost in scores of this size)
+    torch.testing.assert_close(out, mean, rtol=1e-5, atol=1e-5)
