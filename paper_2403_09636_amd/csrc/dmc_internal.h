@@ -46,6 +46,51 @@ struct Layout {
   bool v_trans;           // value pages stored transposed (matrix-core decode)
 };
 
+// Most slots at capacity for which a decode step of a layer runs as one workgroup
+// per unit (short caches), in one launch.  In bytes of K and V: 256 KB.  One
+// compute unit streams about 50 KB/us (measured, 4 or 16 waves), so the longest
+// unit takes 5 us, which is what the slot-space table and the combine launch of
+// the general path cost.  Four fp32 units of up to 64 slots: 5.3 + 7.8 (combine)
+// -> 3.8 us per step.  Exceptions, us per step, the general path -> one launch:
+// - Matrix cores (vt: bf16, groups of 4 and 8, pages of 32 slots): the general
+//   path copies each chunk of a piece through its ring before the first product,
+//   so from 64 units, which keep enough memory requests in flight, 512 KB are
+//   still faster (1022 slots, d = 128, G = 8: 64 units 24.9 -> 20.9, 128 29.3 ->
+//   22.1, 256 39.5 -> 30.8; 32 units would lose, 343 -> 360 for a prompt and 16
+//   steps).
+// - bf16 groups of 4 and 8 on the vector ALUs are bound by their arithmetic, as is
+//   the general path once its waves fill the chip.  G = 4, pages of 16: 64 units of
+//   510 slots at d = 128 would go 19.8 -> 22.3, of 1020 at d = 64 19.7 -> 28.4, but
+//   253 slots go 18.5 -> 15.7 and 17.9 -> 14.4; 192 units of 510 slots go 26.1 ->
+//   23.1 and 21.7 -> 18.5; 256 of 1022 at d = 128 38.9 -> 38.8, half full 28.4 ->
+//   24.2.  G = 8: 64 units of 1020 slots at d = 64 would go 35.5 -> 40.7, 96 of 1022
+//   at d = 128 48.0 -> 55.2; 128 and 256 units of 1022 go 52.4 -> 55.8 and 76.5 ->
+//   57.5, half full 41.9 -> 34.7 and 54.7 -> 36.3.
+// fp32 groups stay at 256 KB: 64 units of 508 slots at d = 64, G = 4 lose (17.2 ->
+// 19.3), but a quarter full they gain (15 -> 10.1), as do all other layers measured.
+constexpr inline int64_t one_launch_slots(int elem_bytes, int head_dim, int group, bool vt, int64_t units) {
+  const int64_t slots = (256 << 10) / (2 * head_dim * elem_bytes);   // 256 KB
+  if (vt) return units >= 64 ? 2 * slots : slots;
+  if (elem_bytes == 2 && group == 4) {
+    const int64_t most = units >= 240 ? 1024 : units >= 192 ? 512 : 256;
+    return most < 2 * slots ? most : 2 * slots;
+  }
+  if (elem_bytes == 2 && group == 8) {
+    if (units >= 128) return 2 * slots;
+    return slots < 768 ? slots : 768;
+  }
+  return slots;
+}
+
+// Whether a layer's decode steps take that path: up to 256 units, so that the
+// workgroups are all resident at once, one per compute unit.  The declared
+// capacity decides, not the lengths.
+constexpr inline bool decode_one_launch(int elem_bytes, int head_dim, int group, bool vt, int64_t units,
+                                        int64_t max_slots, int split_tile) {
+  return split_tile == 0 && units <= 256 &&
+         max_slots <= one_launch_slots(elem_bytes, head_dim, group, vt, units);
+}
+
 // Window grouping: per unit, a ring of `window` raw tokens of its open
 // segment (token j of the segment in entry j mod window): a key row with
 // element 0 zeroed, then a value row, in the cache dtype; their omegas

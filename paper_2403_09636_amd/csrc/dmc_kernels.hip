@@ -17,7 +17,7 @@
 //
 // Decode = one fused launch per layer (Algorithm 1 update + split-K
 // attention, balanced by actual compressed length) plus a small combine
-// launch for units split over several pieces.  Short caches (unit_bytes) run
+// launch for units split over several pieces.  Short caches (decode_one_launch) run
 // the fused launch alone, one workgroup per unit, and its owners write their
 // lengths to buffer 0 (no other workgroup reads them).
 #include "dmc_device.h"
@@ -2432,25 +2432,6 @@ void launch_decode_kernel(const DecodeParams &p, int grid, bool vt, size_t lds, 
   hipLaunchKernelGGL((decode_kernel<ES, D, G, WIN, GRP, UNIT>), dim3(vgrid), dim3(NT), lds, s, p);
 }
 
-// Largest K and V bytes of a unit at capacity, and units, for which a decode
-// step runs as one workgroup per unit.  One compute unit streams about 50 KB/us
-// (measured, 4 or 16 waves), so the longest unit of 256 KB takes 5 us, which is
-// what the slot-space table and the combine launch of the general path cost; and
-// up to 256 units the workgroups are all resident at once, one per compute unit.
-// Four fp32 units of up to 64 slots: 5.3 + 7.8 (combine) -> 3.8 us per step.
-// On the matrix cores the general path costs more (it copies each chunk of a
-// piece through its ring before the first product), so from kUnitWideUnits units,
-// which keep enough memory requests in flight, 512 KB are still faster.  A pass
-// of prefill and 16 steps at 1000 tokens, two layouts of 4 and 8 query heads per
-// kv head: 64 units 357 -> 322 us, 128 421 -> 380, 256 545 -> 462 (700 tokens:
-// 472 -> 378); 32 units would go from 343 to 360 and 8 from 305 to 339.
-template <int ES, int G>
-constexpr int64_t unit_bytes(int units) {
-  constexpr int kUnitBytes = 256 << 10, kUnitWideUnits = 64;
-  return ES == 2 && G >= 4 && units >= kUnitWideUnits ? 2 * kUnitBytes : kUnitBytes;
-}
-constexpr int kUnitMaxUnits = 256;
-
 // Heads up to which the combine takes a workgroup each (their waves are all
 // resident at once, and only such layers split units into many pieces).
 constexpr int kWideCombineHeads = 1024;
@@ -2461,8 +2442,7 @@ hipError_t decode_impl(const DecodeParams &p, int grid, bool vt, hipStream_t s) 
                                       p.win.window > 0);
   if (vt && !(ES == 2 && G >= 4)) return hipErrorInvalidValue;
   // Short caches: one workgroup per unit, one launch per step.
-  if (p.split_tile == 0 && p.units <= kUnitMaxUnits &&
-      int64_t(p.max_slots) * 2 * D * ES <= unit_bytes<ES, G>(p.units)) {
+  if (decode_one_launch(ES, D, G, vt, p.units, p.max_slots, p.split_tile)) {
     const size_t unit_lds = decode_lds_bytes(0, G, D, p.win.window > 0);
     if (p.win.window > 0)
       launch_decode_kernel<ES, D, G, true, false, true>(p, p.units, vt, unit_lds, s);

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", 64, 2, 16, 300), ("bf16", 128, 8, 32, 259), ("bf16", 64, 4, 32, 1024),
     ("bf16", 128, 4, 64, 200),
     ("bf16", 128, 8, 32, 1000), ("bf16", 128, 4, 32, 1024),   # (80 units: the wider limit)
+    ("bf16", 128, 4, 16, 256), ("bf16", 64, 8, 64, 768),      # (vector ALUs at their limits)
 ])
 def test_unit_decode_matches_general(torch_cuda, dtype, d, G, page, cap):
     import torch
