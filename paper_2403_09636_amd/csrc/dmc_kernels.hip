@@ -1000,14 +1000,17 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
         for (int nt = 0; nt < NT; ++nt) acc[nt] *= f;
         m = mn;
         // Leading bits (truncated) and the rest, which is kept positive so that an
-        // infinite value stays one (2^-100 of a finite one is lost in the sum).
+        // infinite value stays one: at least 2^-100 (lost in the sum beside a larger
+        // leading term), but no more than the leading term, so that a vanished
+        // probability is 0 in both.
         uint32_t pw[4];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
           const float p0 = fast_exp2(sv[2 * w] - mn), p1 = fast_exp2(sv[2 * w + 1] - mn);
           const uint32_t h0 = __float_as_uint(p0) & 0xffff0000u, h1 = __float_as_uint(p1) & 0xffff0000u;
-          const uint32_t rest = cvt_pk_bf16(fmaxf(p0 - __uint_as_float(h0), 0x1p-100f),
-                                            fmaxf(p1 - __uint_as_float(h1), 0x1p-100f));
+          const float f0 = __uint_as_float(h0), f1 = __uint_as_float(h1);
+          const uint32_t rest = cvt_pk_bf16(fmaxf(p0 - f0, fminf(f0, 0x1p-100f)),
+                                            fmaxf(p1 - f1, fminf(f1, 0x1p-100f)));
           pw[w] = (n & G) ? rest : (h0 >> 16) | h1;
           ls += p0 + p1;
         }

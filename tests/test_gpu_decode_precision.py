@@ -82,3 +82,28 @@ def test_infinite_values_stay_infinite(torch_cuda):
         want = torch.zeros_like(out)
         want[0, G:2 * G, 5], want[1, 2 * G:3 * G, 127] = math.inf, -math.inf
         assert torch.equal(torch.where(out.isinf(), out, 0), want) and not out.isnan().any()
+
+
+def test_vanished_probability_adds_nothing(torch_cuda):
+    """A slot whose probability is 0 in 32 bits (a score thousands below the largest)
+    adds nothing, however large its value."""
+    import torch
+    import paper_2403_09636_amd as P
+    B, Hkv, G, d, cap = 2, 4, 8, 128, 700
+    gen = torch.Generator().manual_seed(5)
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=gen).to(torch.bfloat16)
+
+    K, V, q, k, v = rnd(B, Hkv, cap, d), rnd(B, Hkv, cap, d), rnd(B, Hkv * G, d), rnd(B, Hkv, d), rnd(B, Hkv, d)
+    K[..., 0], k[..., 0] = 0, -4
+    q[..., 1] = 200
+    K[:, :, 9, 1], V[:, :, 9] = -200, 1e38
+    lens = torch.full((B, Hkv), cap - 2, dtype=torch.int32)
+    want = exact(q, k, v, K, V, lens, G)
+    assert want.abs().max() < 100
+    for split in (0, 100):
+        cache = P.DMCCache(P.make_config(1, B, Hkv * G, Hkv, d, "bf16", max_slots_per_seq=cap, split_tile=split))
+        cache.import_(0, K.cuda(), V.cuda(), lens.cuda(), torch.ones((B, Hkv), device="cuda"))
+        out = cache.decode_step(0, q.cuda(), k.cuda(), v.cuda()).cpu().double()
+        torch.testing.assert_close(out, want, rtol=1e-2, atol=2e-2)
