@@ -1,11 +1,13 @@
 """GPU: dmc_decode_step captured in a HIP graph and replayed.
 
-Every decode call of a layer uses the same device buffers (the step's last
-kernel copies the post-step lengths back), so a graph of one step -- the
-usual serving graph, one step per layer per token -- replays correctly, and
-so does one of two steps.  Each replay must equal the same number of eager
-steps on a second cache with the same inputs, bit for bit, with eager work
-and synchronisations between replays.
+Every decode call of a layer uses the same device buffers, so a graph of one
+step -- the usual serving graph, one step per layer per token -- replays
+correctly, and so does one of two steps.  Short caches run one launch, whose
+workgroups write their units' lengths in place; longer ones run two, the
+second of which copies the post-step lengths back.  Both are replayed here (a
+capacity of 1100 slots is past the one-launch limits).  Each replay must equal
+the same number of eager steps on a second cache with the same inputs, bit for
+bit, with eager work and synchronisations between replays.
 """
 import numpy as np
 import pytest
@@ -15,13 +17,14 @@ from tests.gpu_helpers import f64, log, random_step
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("dense", [100, 1084])   # one launch per step, two
 @pytest.mark.parametrize("nsteps", [1, 2])
 @pytest.mark.parametrize("G", [1, 8])
-def test_decode_graph_replay(torch_cuda, G, nsteps):
+def test_decode_graph_replay(torch_cuda, G, nsteps, dense):
     import torch
     import paper_2403_09636_amd as P
-    log(f"case graph replay G={G} steps per graph={nsteps}")
-    B, Hkv, d, dense = 4, 4, 128, 100
+    log(f"case graph replay G={G} steps per graph={nsteps} slots={dense + 16}")
+    B, Hkv, d = 4, 4, 128
     Hq = Hkv * G
     rng = np.random.default_rng(300 + G)
     lens = torch.from_numpy(rng.integers(60, dense + 1, size=(B, Hkv)).astype(np.int32)).cuda()
