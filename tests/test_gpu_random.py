@@ -7,7 +7,9 @@ per-head compression ratios, decision bias, importance source, decision
 source, window and forced split independently, so that combinations the
 grids skip are exercised too: pages of 8 or 16 slots under grouped queries,
 ragged tails in every block and chunk loop, stream-K ranges cut inside
-units, empty and one-token prompts next to long ones."""
+units, empty and one-token prompts next to long ones.  Caches of that size
+decode in one launch unless a split is forced; further seeds declare a larger
+capacity, so that the general path (equal ranges, pieces, combine) runs too."""
 import numpy as np
 import pytest
 
@@ -17,6 +19,8 @@ from workloads import decision_logits
 pytestmark = pytest.mark.gpu
 
 CASES = 256
+LARGE_CASES = 64
+LARGE_CAPACITY = 2304   # slots, past every one-launch limit
 
 
 def _draw(seed):
@@ -47,12 +51,23 @@ def _draw(seed):
 
 @pytest.mark.parametrize("seed", range(CASES))
 def test_random_configuration(torch_cuda, seed):
+    _run(seed, 0)
+
+
+@pytest.mark.parametrize("seed", range(CASES, CASES + LARGE_CASES))
+def test_random_configuration_large_capacity(torch_cuda, seed):
+    _run(seed, LARGE_CAPACITY)
+
+
+def _run(seed, capacity):
     import torch
     rng, c = _draw(seed)
-    log(f"case random seed={seed} {c}")
+    if capacity:
+        c["split"] = 0
+    log(f"case random seed={seed} capacity={capacity} {c}")
     B, n, Hkv, G, d, dtype = c["B"], c["n"], c["Hkv"], c["G"], c["d"], c["dtype"]
     steps = 4
-    pr = Pair(1, B, Hkv * G, Hkv, d, dtype, page_size=c["page"], max_slots=n + steps + 8,
+    pr = Pair(1, B, Hkv * G, Hkv, d, dtype, page_size=c["page"], max_slots=max(n + steps + 8, capacity),
               bias=c["bias"], omega_src=c["omega"], split_tile=c["split"], max_prompt_len=n,
               decision_src=c["decision"], window=c["window"])
     dt = torch.float32 if dtype == "fp32" else torch.bfloat16
