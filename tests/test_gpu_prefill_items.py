@@ -5,7 +5,8 @@ importances averaged over a group -- against the oracle."""
 import numpy as np
 import pytest
 
-from tests.gpu_helpers import Pair, log, torch_dtype
+import oracle
+from tests.gpu_helpers import Pair, assert_close, f64, log, torch_dtype
 from workloads import decision_logits
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +45,57 @@ def test_prefill_items(torch_cuda, dtype, B, Hq, Hkv, d, page, n, crs, window, o
                  for h in (Hq, Hkv, Hkv))
     pair.decode(0, q, kk, vv)
     pair.ok()
+
+
+@pytest.mark.parametrize("d,omega,attend", [(64, "group_mean", False), (128, "lead", True)])
+def test_full_items_staged(torch_cuda, d, omega, attend):
+    """128-token items (units * n above 6144 * 112) on transposed value pages with staged
+    importances: every unit's slot indices and lengths against the decisions, sampled
+    units' caches (and prompt outputs) against a per-unit oracle."""
+    import torch
+    import paper_2403_09636_amd as P
+    B, Hq, Hkv, n, G = 44, 16, 4, 4096, 4
+    log(f"case full items d={d} {omega} attend={attend}")
+    gen = torch.Generator(device="cuda").manual_seed(d)
+
+    def rnd(heads):
+        return torch.randn((B, n, heads, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+
+    k, v, q = rnd(Hkv), rnd(Hkv), rnd(Hq)
+    rng = np.random.default_rng(d)
+    k0 = decision_logits(rng.uniform(size=(B, n, Hkv)), np.array([1, 2, 9, 1e9])[None, None])
+    k[..., 0] = torch.from_numpy(k0).to(k)
+    lens = rng.integers(n // 2, n + 1, size=B)
+    lens[0] = n
+    cache = P.DMCCache(P.make_config(1, B, Hq, Hkv, d, "bf16", max_slots_per_seq=n, max_prompt_len=n,
+                                     omega_src=omega))
+    slot = torch.empty((B, Hkv, n), dtype=torch.int32, device="cuda")
+    lens_t = torch.as_tensor(lens, dtype=torch.int32, device="cuda")
+    if attend:
+        out = cache.prefill_attend(0, k, v, q, prompt_lens=lens_t, slot_index=slot)
+    else:
+        cache.prefill(0, k, v, q, prompt_lens=lens_t, slot_index=slot)
+    cache.check()
+    alpha = oracle.decision(f64(k[..., 0]), 0.0)
+    alpha[:, 0] = 0
+    want = (np.cumsum(1 - alpha, axis=1) - 1).transpose(0, 2, 1)
+    want = np.where(np.arange(n) < lens[:, None, None], want, -1)
+    assert (slot.cpu().numpy() == want).all()
+    lengths = cache.lengths(0).cpu().numpy()
+    assert (lengths == want.max(axis=2) + 1).all()
+    K, V, z = cache.export(0, dense_slots=n)
+    for b, g in [(0, 0), (0, 1), (17, 2), (30, 3), (43, 1)]:
+        m, hs = int(lens[b]), slice(g * G, (g + 1) * G)
+        orc = oracle.DMCOracle(1, 1, G, 1, d, max_slots=n, omega_src=omega)
+        kb, vb, qb = f64(k[b:b + 1, :m, g:g + 1]), f64(v[b:b + 1, :m, g:g + 1]), f64(q[b:b + 1, :m, hs])
+        if attend:
+            o_ref, _ = orc.prefill_attend(0, qb, kb, vb)
+            assert_close(f64(out[b, :m, hs]), o_ref[0], "bf16", f"outputs of unit {(b, g)}")
+            assert (out[b, m:, hs] == 0).all()
+        else:
+            orc.prefill(0, kb, vb, qb[..., 0])
+        K_ref, V_ref, l_ref, z_ref = orc.export(0)
+        l = int(l_ref[0, 0])
+        assert_close(f64(K[b, g, :l]), K_ref[0, 0, :l], "bf16", f"keys of unit {(b, g)}")
+        assert_close(f64(V[b, g, :l]), V_ref[0, 0, :l], "bf16", f"values of unit {(b, g)}")
+        assert np.isclose(float(z[b, g]), z_ref[0, 0], rtol=1e-4)
