@@ -1,6 +1,7 @@
 """GPU: distance of the decode outputs from the 64-bit values.  What rounding the
 output to bf16 gives by itself is the bound, within a tenth, however a unit's
-slots are cut: the probabilities of the value product carry more than 16 bits."""
+slots are cut: the probabilities of the value product carry more than 16 bits.
+fp32 outputs: the rounding of the sums."""
 import math
 
 import pytest
@@ -107,3 +108,34 @@ def test_vanished_probability_adds_nothing(torch_cuda):
         cache.import_(0, K.cuda(), V.cuda(), lens.cuda(), torch.ones((B, Hkv), device="cuda"))
         out = cache.decode_step(0, q.cuda(), k.cuda(), v.cuda()).cpu().double()
         torch.testing.assert_close(out, want, rtol=1e-2, atol=2e-2)
+
+
+# Equal ranges of short and of split units, one workgroup per unit.  Limits (in 2^-24, inputs and
+# kernels repeat exactly): between what chunks summed by themselves give (2.43, 2.69, 2.65, 2.46)
+# and chains over a whole piece (2.66, 2.88, 2.92, 2.76).
+@pytest.mark.parametrize("B,Hkv,G,d,cap,slots,limit", [
+    (60, 8, 1, 128, 200, 100, 2.55), (20, 8, 2, 128, 1200, 400, 2.8), (12, 4, 8, 128, 250, 240, 2.8),
+    (8, 4, 1, 64, 500, 480, 2.6),
+])
+def test_fp32_error(torch_cuda, B, Hkv, G, d, cap, slots, limit):
+    import torch
+    import paper_2403_09636_amd as P
+    log(f"case fp32 decode precision B={B} Hkv={Hkv} G={G} d={d} slots={slots}")
+    gen = torch.Generator().manual_seed(cap + G)
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=gen)
+
+    K, V = rnd(B, Hkv, cap, d), rnd(B, Hkv, cap, d)
+    K[..., 0] = 0
+    lens = torch.randint(slots // 2, slots, (B, Hkv), generator=gen, dtype=torch.int32)
+    q, k, v = rnd(B, Hkv * G, d), rnd(B, Hkv, d), rnd(B, Hkv, d)
+    k[..., 0] = -4   # append
+    cache = P.DMCCache(P.make_config(1, B, Hkv * G, Hkv, d, "fp32", max_slots_per_seq=cap))
+    cache.import_(0, K.cuda(), V.cuda(), lens.cuda(), torch.ones((B, Hkv), device="cuda"))
+    got = cache.decode_step(0, q.cuda(), k.cuda(), v.cuda()).cpu().double()
+    cache.check()
+    want = exact(q, k, v, K, V, lens, G)
+    err = float((got - want).norm() / want.norm()) * 2 ** 24
+    log(f"error {err:.3f} x 2^-24")
+    assert err <= limit
