@@ -358,6 +358,7 @@ dmc_status decode_params(dmc_cache *cache, int32_t layer, const void *q, const v
   p.units = L.units;
   p.hkv = c.num_kv_heads;
   p.hq = c.num_q_heads;
+  p.compute_units = cache->cu_count;
   p.maxpages = L.maxpages;
   p.max_slots = c.max_slots_per_seq;
   p.log2p = ilog2(c.page_size);

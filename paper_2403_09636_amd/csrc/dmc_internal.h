@@ -91,6 +91,22 @@ constexpr inline bool decode_one_launch(int elem_bytes, int head_dim, int group,
          max_slots <= one_launch_slots(elem_bytes, head_dim, group, vt, units);
 }
 
+// First slot-space range of a decode wave (its others follow at steps of all the
+// launch's waves); nranges for a wave without any.  Few ranges go one to a
+// workgroup before the second of any, to the first `workgroups` of the grid: as
+// many as certainly run at once.  The vector-ALU kernels of many registers hold
+// one workgroup per compute unit where the grid has two; ranges dealt to the
+// whole grid then took two rounds.  us per step, in rounds -> at once: 320 units
+// of 60 slots, fp32, 8 query heads per kv head, d = 128: 42.3 -> 26.5; 64 units
+// of 250, bf16, 8 heads, pages of 16, d = 64: 32.9 -> 20.3.  Filling workgroup
+// after workgroup instead leaves compute units idle (8 units of 2000 slots,
+// bf16, one head: 11.1 -> 12.4).
+constexpr inline int first_range(int nranges, int grid, int waves, int workgroups, int block, int wave) {
+  const int most = grid < workgroups ? grid : workgroups;
+  if (2 * nranges > grid * waves || nranges > most * waves) return block * waves + wave;
+  return block < most ? wave * most + block : nranges;
+}
+
 // Window grouping: per unit, a ring of `window` raw tokens of its open
 // segment (token j of the segment in entry j mod window): a key row with
 // element 0 zeroed, then a value row, in the cache dtype; their omegas
@@ -123,6 +139,7 @@ struct DecodeParams {
   float scale_log2;        // log2(e) / sqrt(d)
   int32_t units, hkv, hq, maxpages, max_slots, log2p, split_tile, omega_src, decision_src;
   int32_t slot_group;      // units per entry of the slot-space table in LDS (1, or 2..64)
+  int32_t compute_units;
 };
 
 struct PrefillParams {

@@ -351,8 +351,7 @@ __global__ __launch_bounds__((valu_decode_threads<ES, G>())) void decode_kernel(
     nranges = (S + span - 1) / span;
   }
 
-  // (few ranges: one per workgroup before the second of any)
-  const int r_first = UNIT ? 0 : 2 * nranges <= nwaves ? wave * gridDim.x + blockIdx.x : blockIdx.x * NW + wave;
+  const int r_first = UNIT ? 0 : first_range(nranges, gridDim.x, NW, p.compute_units, blockIdx.x, wave);
   for (int r = r_first; r < nranges; r += UNIT ? 1 : nwaves) {
     int pos = UNIT ? 0 : r * span;
     const int pos_end = UNIT ? 1 : min(pos + span, S);
@@ -934,8 +933,8 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
     if (!pieces) nranges = whole ? nwaves : (S + span - 1) / span;
   }
 
-  // (few ranges: one per workgroup before the second of any)
-  const int r_first = UNIT ? 0 : 2 * nranges <= nwaves ? wave * gridDim.x + blockIdx.x : blockIdx.x * kWaves + wave;
+  // (the grid's workgroups all run at once)
+  const int r_first = UNIT ? 0 : first_range(nranges, gridDim.x, kWaves, gridDim.x, blockIdx.x, wave);
   for (int r = r_first; r < nranges; r += UNIT ? 1 : nwaves) {
     const int wu0 = whole ? static_cast<int>(int64_t(r) * U / nwaves) : 0;
     // positions of the range; pieces count as one position each
