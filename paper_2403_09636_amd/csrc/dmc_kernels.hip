@@ -1418,9 +1418,9 @@ __global__ __launch_bounds__(kThreads, mfma_decode_wg_per_cu<D>()) void decode_m
 // i's max and sum, broadcast by v_readlane), R = 4 for the usual case, 8, or
 // batches of 16.  Short and uneven layers split their long units into tens of
 // pieces; they have few heads, so there (WIDE) a workgroup's four waves share a
-// head's batches and merge in LDS.  One chat request (32 heads, up to 60 records
-// before ranges had a least size of 32 slots): 13.3 -> 4.2 us per launch; 240
-// uneven heads, up to 61 records: 7.9 -> 4.8 us.  The launch also copies the
+// head's batches and merge in LDS.  At equal record counts, against one record
+// after the other: 32 heads of 33 records 8.6 -> 4.2 us per launch, 240 heads of
+// 61 records 8.7 -> 4.8 us.  The launch also copies the
 // step's post-update lengths back into the layer's current-lengths buffer
 // (every unit's owner wrote len_out; this launch runs after all of them).
 template <int ES, int D, int G, bool WIDE>
