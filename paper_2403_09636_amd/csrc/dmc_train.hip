@@ -1125,8 +1125,13 @@ __device__ __forceinline__ uint32_t row_offset(int row, int ks, int hb) {
 // (rank 0) first, so that they share the unit's states in L2 -- but with one
 // query head per kv head the last kTailUnits units are interleaved, every unit's
 // heaviest tile before any unit's second, so that no heavy tile starts when the
-// XCD is running dry (64 units of 4096 tokens: 1899 -> 1750 us per forward and
-// backward).  Grouped query heads keep unit order: their
+// XCD is running dry.  Forward and backward, us, in unit order / with the last 8
+// interleaved / with all interleaved, d = 128: 8 units per XCD of 2048 tokens 722 /
+// 640 / 630, 12 of 1999 888 / 791 / 808, 16 of 2048 1218 / 1158 / 1109, 16 of 4096
+// 3514 / 3403 / 3354, 32 of 1024 900 / 848 / 860, 32 of 2048 2226 / 2208 / 2267; d = 64:
+// 16 of 4096 2063 / 1938 / 1940, 20 of 1500 593 / 515 / 505.  Eight is within 5 % of
+// the best of the two everywhere; all interleaved loses to unit order where many
+// units' states exceed the L2.  Grouped query heads keep unit order: their
 // tiles hold fewer tokens and read the states more often per product (24 units
 // of 1501 tokens, G = 4: 614 us against 621 interleaved).
 constexpr int kTailUnits = 8;
