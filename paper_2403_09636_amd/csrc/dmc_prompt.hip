@@ -746,7 +746,7 @@ __global__ __launch_bounds__(kThreads, 2) void prompt_mfma_kernel(PromptParams p
 // omega for the rows of a column's open segment and 0 elsewhere:
 //   score(t) = sum_j w_tj (q_t . k_j) / z_t,   value(t) = sum_j w_tj v_j / z_t.
 // Bound by the longest tile's chain of blocks and the fp32 matrix rate: prompt
-// of 777 tokens, batch 3, 16/8 heads, d = 64: 906 -> 37 us against one wave per
+// of 777 tokens, batch 3, 16/8 heads, d = 64: 912 -> 41 us against one wave per
 // 8 query rows on the vector ALUs (a cross-lane reduction per score).
 // ---------------------------------------------------------------------------
 template <int D, int G>
