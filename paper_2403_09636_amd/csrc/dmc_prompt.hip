@@ -28,6 +28,11 @@
 namespace dmc {
 namespace {
 
+__device__ __forceinline__ float wave_sum(float x) {
+  x = row_sum<32>(x);
+  return x + __shfl_xor(x, 32, 64);
+}
+
 __device__ __forceinline__ int wave_sum_int(int x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
@@ -53,12 +58,72 @@ __device__ __forceinline__ int token_slots(const PromptParams &p, int u, int a, 
   return lane < cnt ? before + __popcll(mine & upto) - 1 : -1;
 }
 
+// Rebuilds the open-segment running sums of tokens [a, a + cnt) (cnt >= 1)
+// in token order, starting at the 32-token boundary at or below a: calls
+// snap(t, ak, av, zs) for every t >= a with the sums after token t, and
+// batch_end(t0) after each batch of 8 tokens t0 .. t0 + 7.  Lanes own
+// elements lane * E .. lane * E + E - 1; k[0] is read as 0.
+template <int ES, int D, typename Snap, typename BatchEnd>
+__device__ __forceinline__ void walk_open_state(const PromptParams &p, int u, int b, int g, int a,
+                                                int cnt, Snap &&snap, BatchEnd &&batch_end) {
+  constexpr int E = D / 64;
+  constexpr int kRows = 8;
+  const int lane = threadIdx.x & 63;
+  const int bs = a & ~31, end = a + cnt;
+  const uint8_t *al = p.alpha + int64_t(u) * p.max_prompt;
+  const float *om = p.omega + int64_t(u) * p.max_prompt;
+  float ak[E], av[E], zs = 0.0f;
+#pragma unroll
+  for (int e = 0; e < E; ++e) ak[e] = av[e] = 0.0f;
+  if (bs > 0 && al[bs] != 0) {   // the segment open at bs started earlier
+    const float *cr = p.carry + (int64_t(u) * p.carry_blocks + (bs >> 5)) * carry_stride(D);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      ak[e] = cr[lane * E + e];
+      av[e] = cr[D + lane * E + e];
+    }
+    zs = cr[2 * D];
+  }
+  const char *kbase = static_cast<const char *>(p.k) + (b * p.ks[0] + g * p.ks[2] + lane * E) * ES;
+  const char *vbase = static_cast<const char *>(p.v) + (b * p.vs[0] + g * p.vs[2] + lane * E) * ES;
+  const int64_t kst = p.ks[1] * ES, vst = p.vs[1] * ES;
+  for (int t0 = bs; t0 < end; t0 += kRows) {
+    float kk[kRows][E], vv[kRows][E], ww[kRows];
+    bool st[kRows];
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const int tj = min(t0 + j, end - 1);
+      load_e<ES, E>(kbase + tj * kst, kk[j]);
+      load_e<ES, E>(vbase + tj * vst, vv[j]);
+      ww[j] = om[tj];
+      st[j] = al[tj] == 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const int tj = t0 + j;
+      if (tj < end) {
+        if (st[j]) {
+          zs = 0.0f;
+#pragma unroll
+          for (int e = 0; e < E; ++e) ak[e] = av[e] = 0.0f;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const float kv = (lane * E + e == 0) ? 0.0f : kk[j][e];   // k_t[0] <- 0
+          ak[e] = fmaf(ww[j], kv, ak[e]);
+          av[e] = fmaf(ww[j], vv[j][e], av[e]);
+        }
+        zs += ww[j];
+        if (tj >= a) snap(tj, ak, av, zs);
+      }
+    }
+    batch_end(t0);
+  }
+}
+
 // Window grouping (Sec. 3.3): the open state of token t is the omega-
 // weighted mean of its segment's tokens max(segment start, t - w + 1) .. t.
-// Rebuilds it for tokens [a, a + cnt) (cnt >= 1) in token order: calls
-// snap(t, ak, av, zs) for every t >= a with the sums up to token t, and
-// batch_end(t0) after each batch of 8 tokens t0 .. t0 + 7.  Lanes own
-// elements lane * E .. lane * E + E - 1; k[0] is read as 0.  The walk starts at the 8-aligned token
+// Same interface as walk_open_state.  The walk starts at the 8-aligned token
 // at or below a - w + 1 with empty sums (no carry records: a window never
 // reaches further back), adds each token, restarts at segment starts and
 // removes the token that leaves the window (t - w, when it lies in the
@@ -947,6 +1012,128 @@ __global__ __launch_bounds__(kThreads) void prompt_f32_kernel(PromptParams p, in
   }
 }
 
+// ---------------------------------------------------------------------------
+// fp32 prompts of few tokens, on the vector ALUs.  One wave = one unit's
+// TG = max(1, 8 / G) tokens with all G heads of the group (R = TG * G <= 8
+// query rows); lanes own head-dim elements; closed slots stream row by row
+// with R online-softmax states.  No fixed cost to speak of, where a column tile
+// of prompt_f32_kernel takes about 15 us whatever it holds and two of them fill
+// a compute unit's LDS at d = 128 (prompt_f32_short draws the line).
+// ---------------------------------------------------------------------------
+template <int ES, int D, int G>
+__global__ __launch_bounds__(kThreads) void prompt_valu_kernel(PromptParams p, int ngroups) {
+  constexpr int TG = G >= 8 ? 1 : 8 / G;
+  constexpr int R = TG * G;
+  constexpr int E = D / 64;
+  constexpr int RB = D * ES;
+  constexpr int kAhead = 4;   // slot rows in flight
+  const int lane = threadIdx.x & 63;
+  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int u = wid / ngroups;
+  if (u >= p.units) return;
+  const int grp = wid - u * ngroups;
+  const int b = u / p.hkv, g = u - b * p.hkv;
+  const int nb = clamp_prompt_len(p.prompt_lens, p.n, b);
+  const bool ok = p.page_base[u] >= 0;
+  const int a = grp * TG;
+  const int cnt = ok ? max(0, min(TG, nb - a)) : 0;
+
+  float qr[R][E];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = r / G, h = r - j * G;
+#pragma unroll
+    for (int e = 0; e < E; ++e) qr[r][e] = 0.0f;
+    if (j < cnt)
+      load_e<ES, E>(static_cast<const char *>(p.q) +
+                        (b * p.qs[0] + int64_t(a + j) * p.qs[1] + (g * G + h) * p.qs[2] + lane * E) * ES,
+                    qr[r]);
+    if (lane == 0) qr[r][0] = 0.0f;   // q[0] is not part of the score
+  }
+
+  float m[R], l[R], acc[R][E];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    m[r] = 0.0f;
+    l[r] = 1.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[r][e] = 0.0f;
+  }
+  int seg = -1, lim[TG];
+  if (cnt > 0) {
+    seg = token_slots(p, u, a, cnt);
+    auto snap = [&](int t, const float *ak, const float *av, float zs) {
+          const float inv = 1.0f / zs;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            if (a + r / G != t) continue;
+            float d = 0.0f;
+#pragma unroll
+            for (int e = 0; e < E; ++e) d = fmaf(qr[r][e], ak[e] * inv, d);
+            m[r] = wave_sum(d) * p.scale_log2;
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[r][e] = av[e] * inv;
+          }
+        };
+    if (p.window > 0)
+      walk_window_state<ES, D>(p, u, b, g, a, cnt, snap, [](int) {});
+    else
+      walk_open_state<ES, D>(p, u, b, g, a, cnt, snap, [](int) {});
+  }
+  int hi = 0;
+#pragma unroll
+  for (int j = 0; j < TG; ++j) {
+    const int sj = __shfl(seg, j, 64);
+    lim[j] = j < cnt ? sj : 0;
+    hi = max(hi, lim[j]);
+  }
+  const int P = 1 << p.log2p;
+  const int64_t pt = int64_t(u) * p.maxpages;
+  for (int s0 = 0; s0 < hi; s0 += kAhead) {
+    float kk[kAhead][E], vv[kAhead][E];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int s = min(s0 + i, hi - 1);
+      const char *row = p.pool + int64_t(p.ptab[pt + (s >> p.log2p)]) * p.page_bytes +
+                        int64_t(s & (P - 1)) * RB + lane * E * ES;
+      load_e<ES, E>(row, kk[i]);
+      load_e<ES, E>(row + int64_t(P) * RB, vv[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int s = s0 + i;
+      if (s >= hi) break;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (s >= lim[r / G]) continue;
+        float d = 0.0f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) d = fmaf(qr[r][e], kk[i][e], d);
+        const float x = wave_sum(d) * p.scale_log2;
+        const float mn = fmaxf(m[r], x);
+        const float f = fast_exp2(m[r] - mn), w = fast_exp2(x - mn);
+        l[r] = l[r] * f + w;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[r][e] = fmaf(acc[r][e], f, w * vv[i][e]);
+        m[r] = mn;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = r / G, h = r - j * G;
+    const int t = a + j;
+    if (t >= p.n) continue;
+    float o[E];
+    const float inv = j < cnt ? 1.0f / l[r] : 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = acc[r][e] * inv;
+    store_e<ES, E>(static_cast<char *>(p.out) +
+                       (b * p.os[0] + int64_t(t) * p.os[1] + (g * G + h) * p.os[2] + lane * E) * ES,
+                   o);
+  }
+}
+
 template <int D, int G>
 hipError_t prompt_mfma(const PromptParams &p, bool vt, hipStream_t s) {
   constexpr int TW = kWaves * (32 / G);
@@ -965,10 +1152,36 @@ hipError_t prompt_mfma(const PromptParams &p, bool vt, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int ES, int D, int G>
+hipError_t prompt_valu(const PromptParams &p, hipStream_t s) {
+  constexpr int TG = G >= 8 ? 1 : 8 / G;
+  const int ngroups = (p.n + TG - 1) / TG;
+  const int64_t waves = int64_t(p.units) * ngroups;
+  const int64_t blocks = (waves + kWaves - 1) / kWaves;
+  if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL((prompt_valu_kernel<ES, D, G>), dim3(unsigned(blocks)), dim3(kThreads), 0, s,
+                     p, ngroups);
+  return hipGetLastError();
+}
+
+// Whether an fp32 call of n tokens runs on the vector ALUs: short prompts, where
+// the column tiles of prompt_f32_kernel (32 query rows of a unit each) are mostly
+// empty or too many for their LDS.  us per call with compaction, vector ALUs ->
+// tiles: d = 128, 64 units of 1 token 19 -> 26, of 8 26 -> 27, of 12 31 -> 29; 1024
+// units of 1 token 20 -> 59, of 17 (8 query heads per kv head) 126 -> 266, of 33 308 -> 523, of 64
+// 1164 -> 953; d = 64, 1024 units of 1 token 20 -> 31, of 9 (8 heads) 45 -> 75, of 17 80 -> 116,
+// of 33 180 -> 193, of 64 719 -> 344.
+bool prompt_f32_short(int head_dim, int group, int64_t tiles, int64_t n) {
+  const bool few = group == 8;   // four tokens a tile
+  if (head_dim == 64) return n <= 4 || (n < 32 && tiles > (few ? 3 : 5) * n * n);
+  return n <= 8 || (n <= 40 && n != 32 && tiles > (few ? 14 : 28) * n) || (n <= 48 && tiles > (few ? 2048 : 4096));
+}
+
 template <int D, int G>
 hipError_t prompt_f32(const PromptParams &p, hipStream_t s) {
   const int ntiles = (p.n + 32 / G - 1) / (32 / G);
   const int64_t blocks = int64_t(p.units) * ntiles;
+  if (prompt_f32_short(D, G, blocks, p.n)) return prompt_valu<4, D, G>(p, s);
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((prompt_f32_kernel<D, G>), dim3(unsigned(blocks)), dim3(kThreads), 0, s, p, ntiles);
   return hipGetLastError();
