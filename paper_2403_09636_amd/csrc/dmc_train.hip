@@ -316,6 +316,252 @@ __global__ __launch_bounds__(64) void train_states_mfma_kernel(TrainParams p) {
 }
 
 // ---------------------------------------------------------------------------
+// fp32 attention of short sequences, on the vector ALUs (lanes own head-dim
+// elements, a cross-lane reduction per score).  No fixed cost to speak of, where
+// the tiles below hold 32 rows and mostly padding (train_f32_short draws the line).
+// ---------------------------------------------------------------------------
+
+// Rows handled by one wave of the attention kernels: TG tokens x G heads.
+template <int G>
+struct Rows {
+  static constexpr int TG = G >= 8 ? 1 : 8 / G;
+  static constexpr int R = TG * G;
+};
+
+// Forward attention over the states: one wave per (unit, TG tokens), row r =
+// token a + r / G, head r % G; online softmax in the log2 domain.
+template <int ES, int D, int G>
+__global__ __launch_bounds__(kThreads) void train_fwd_kernel(TrainParams p, int ngroups) {
+  constexpr int TG = Rows<G>::TG, R = Rows<G>::R, E = D / 64, kAhead = 4;
+  const int lane = threadIdx.x & 63;
+  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int U = p.batch * p.hkv;
+  const int u = wid / ngroups;
+  if (u >= U) return;
+  const int a = (wid - u * ngroups) * TG;
+  const int cnt = min(TG, p.n - a);
+  const int b = u / p.hkv, g = u - b * p.hkv;
+  float qr[R][E];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = r / G, h = r - j * G;
+#pragma unroll
+    for (int e = 0; e < E; ++e) qr[r][e] = 0.0f;
+    if (j < cnt)
+      load_e<ES, E>(static_cast<const char *>(p.q) + (row_q(p, b, a + j, g * G + h, D) + lane * E) * ES,
+                    qr[r]);
+    if (lane == 0) qr[r][0] = 0.0f;   // q[0] is not part of the score
+  }
+  float m[R], l[R], acc[R][E];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    m[r] = neg_inf();
+    l[r] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[r][e] = 0.0f;
+  }
+  const int last = a + cnt - 1;
+  const char *ksb = static_cast<const char *>(p.ks) + (int64_t(u) * p.n * D + lane * E) * ES;
+  const char *vsb = static_cast<const char *>(p.vs) + (int64_t(u) * p.n * D + lane * E) * ES;
+  const float *mk = p.mask + int64_t(u) * p.n;
+  for (int s0 = 0; s0 <= last; s0 += kAhead) {
+    float kk[kAhead][E], vv[kAhead][E], bias[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int s = min(s0 + i, last);
+      load_e<ES, E>(ksb + int64_t(s) * D * ES, kk[i]);
+      load_e<ES, E>(vsb + int64_t(s) * D * ES, vv[i]);
+      bias[i] = mk[s] * kLog2e;
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int s = s0 + i;
+      if (s > last) break;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int t = a + r / G;
+        if (r / G >= cnt || s > t) continue;
+        float d = 0.0f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) d = fmaf(qr[r][e], kk[i][e], d);
+        const float x = wsum(d) * p.scale_log2 + (s < t ? bias[i] : 0.0f);
+        const float mn = fmaxf(m[r], x);
+        const float f = fast_exp2(m[r] - mn), w = fast_exp2(x - mn);
+        l[r] = l[r] * f + w;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[r][e] = fmaf(acc[r][e], f, w * vv[i][e]);
+        m[r] = mn;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = r / G, h = r - j * G;
+    if (j >= cnt) continue;
+    float o[E];
+    const float inv = 1.0f / l[r];
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = acc[r][e] * inv;
+    store_e<ES, E>(static_cast<char *>(p.out) + (row_q(p, b, a + j, g * G + h, D) + lane * E) * ES, o);
+    if (lane == 0) p.lse[(int64_t(u) * p.n + a + j) * G + h] = m[r] + __log2f(l[r]);
+  }
+}
+
+// dq of every query row, and D = sum(dout * out) of the row for the state
+// kernel: one wave per (unit, TG tokens), keys streamed as in the forward.
+template <int ES, int D, int G>
+__global__ __launch_bounds__(kThreads) void train_dq_kernel(TrainParams p, int ngroups) {
+  constexpr int TG = Rows<G>::TG, R = Rows<G>::R, E = D / 64, kAhead = 4;
+  const int lane = threadIdx.x & 63;
+  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int U = p.batch * p.hkv;
+  const int u = wid / ngroups;
+  if (u >= U) return;
+  const int a = (wid - u * ngroups) * TG;
+  const int cnt = min(TG, p.n - a);
+  const int b = u / p.hkv, g = u - b * p.hkv;
+  float qr[R][E], dor[R][E], Lr[R], Dr[R], dq[R][E];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = r / G, h = r - j * G;
+#pragma unroll
+    for (int e = 0; e < E; ++e) qr[r][e] = dor[r][e] = dq[r][e] = 0.0f;
+    Lr[r] = 0.0f;
+    Dr[r] = 0.0f;
+    if (j < cnt) {
+      const int64_t ro = row_q(p, b, a + j, g * G + h, D) + lane * E;
+      float of[E];
+      load_e<ES, E>(static_cast<const char *>(p.q) + ro * ES, qr[r]);
+      load_e<ES, E>(static_cast<const char *>(p.dout) + ro * ES, dor[r]);
+      load_e<ES, E>(static_cast<const char *>(p.out) + ro * ES, of);
+      float d = 0.0f;
+#pragma unroll
+      for (int e = 0; e < E; ++e) d = fmaf(dor[r][e], of[e], d);
+      Dr[r] = wsum(d);
+      Lr[r] = p.lse[(int64_t(u) * p.n + a + j) * G + h];
+      if (lane == 0) p.dsum[(int64_t(u) * p.n + a + j) * G + h] = Dr[r];
+    }
+    if (lane == 0) qr[r][0] = 0.0f;
+  }
+  const int last = a + cnt - 1;
+  const char *ksb = static_cast<const char *>(p.ks) + (int64_t(u) * p.n * D + lane * E) * ES;
+  const char *vsb = static_cast<const char *>(p.vs) + (int64_t(u) * p.n * D + lane * E) * ES;
+  const float *mk = p.mask + int64_t(u) * p.n;
+  for (int s0 = 0; s0 <= last; s0 += kAhead) {
+    float kk[kAhead][E], vv[kAhead][E], bias[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int s = min(s0 + i, last);
+      load_e<ES, E>(ksb + int64_t(s) * D * ES, kk[i]);
+      load_e<ES, E>(vsb + int64_t(s) * D * ES, vv[i]);
+      bias[i] = mk[s] * kLog2e;
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int s = s0 + i;
+      if (s > last) break;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int t = a + r / G;
+        if (r / G >= cnt || s > t) continue;
+        float d = 0.0f, dp = 0.0f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          d = fmaf(qr[r][e], kk[i][e], d);
+          dp = fmaf(dor[r][e], vv[i][e], dp);
+        }
+        const float x = wsum(d) * p.scale_log2 + (s < t ? bias[i] : 0.0f);
+        const float pr = fast_exp2(x - Lr[r]);
+        const float ds = pr * (wsum(dp) - Dr[r]);
+#pragma unroll
+        for (int e = 0; e < E; ++e) dq[r][e] = fmaf(ds, kk[i][e], dq[r][e]);
+      }
+    }
+  }
+  const float sc = p.scale_log2 / kLog2e;   // 1 / sqrt(d)
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = r / G, h = r - j * G;
+    if (j >= cnt) continue;
+#pragma unroll
+    for (int e = 0; e < E; ++e) dq[r][e] *= sc;
+    if (lane == 0) dq[r][0] = 0.0f;   // q[0] reaches the loss through omega only (added later)
+    store_e<ES, E>(static_cast<char *>(p.dq) + (row_q(p, b, a + j, g * G + h, D) + lane * E) * ES,
+                   dq[r]);
+  }
+}
+
+// Gradients of the states and of the mask entries: one wave per (unit, KB
+// states), every query row (token >= state, all G heads) streamed.
+template <int ES, int D, int G>
+__global__ __launch_bounds__(kThreads) void train_dkv_kernel(TrainParams p, int nblocks) {
+  constexpr int E = D / 64, KB = 4;
+  const int lane = threadIdx.x & 63;
+  const int wid = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int U = p.batch * p.hkv;
+  const int u = wid / nblocks;
+  if (u >= U) return;
+  const int j0 = (wid - u * nblocks) * KB;
+  const int kc = min(KB, p.n - j0);
+  const int b = u / p.hkv, g = u - b * p.hkv;
+  float kk[KB][E], vv[KB][E], bias[KB], dk[KB][E], dv[KB][E], dm[KB];
+#pragma unroll
+  for (int i = 0; i < KB; ++i) {
+    const int s = j0 + min(i, kc - 1);
+    const int64_t o = (int64_t(u) * p.n + s) * D + lane * E;
+    load_e<ES, E>(static_cast<const char *>(p.ks) + o * ES, kk[i]);
+    load_e<ES, E>(static_cast<const char *>(p.vs) + o * ES, vv[i]);
+    bias[i] = p.mask[int64_t(u) * p.n + s] * kLog2e;
+    dm[i] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) dk[i][e] = dv[i][e] = 0.0f;
+  }
+  for (int t = j0; t < p.n; ++t) {
+    for (int h = 0; h < G; ++h) {
+      const int64_t ro = row_q(p, b, t, g * G + h, D) + lane * E;
+      float qf[E], df[E];
+      load_e<ES, E>(static_cast<const char *>(p.q) + ro * ES, qf);
+      load_e<ES, E>(static_cast<const char *>(p.dout) + ro * ES, df);
+      if (lane == 0) qf[0] = 0.0f;
+      const float L = p.lse[(int64_t(u) * p.n + t) * G + h];
+      const float Dt = p.dsum[(int64_t(u) * p.n + t) * G + h];
+#pragma unroll
+      for (int i = 0; i < KB; ++i) {
+        const int s = j0 + i;
+        if (i >= kc || s > t) continue;
+        float d = 0.0f, dp = 0.0f;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          d = fmaf(qf[e], kk[i][e], d);
+          dp = fmaf(df[e], vv[i][e], dp);
+        }
+        const float x = wsum(d) * p.scale_log2 + (s < t ? bias[i] : 0.0f);
+        const float pr = fast_exp2(x - L);
+        const float ds = pr * (wsum(dp) - Dt);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          dv[i][e] = fmaf(pr, df[e], dv[i][e]);
+          dk[i][e] = fmaf(ds, qf[e], dk[i][e]);
+        }
+        if (s < t) dm[i] += ds;
+      }
+    }
+  }
+  const float sc = p.scale_log2 / kLog2e;
+#pragma unroll
+  for (int i = 0; i < KB; ++i) {
+    if (i >= kc) break;
+    const int64_t o = (int64_t(u) * p.n + j0 + i) * D + lane * E;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      p.dks[o + e] = dk[i][e] * sc;
+      p.dvs[o + e] = dv[i][e];
+    }
+    if (lane == 0) p.dmask[int64_t(u) * p.n + j0 + i] = dm[i];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // fp32 attention, on v_mfma_f32_32x32x2_f32 (operand forms: F32).  One workgroup
 // = 32 columns of one unit -- query columns (token-major: column c is token
 // c / G, head c % G) in the forward and dq, states in the state-gradient kernel
@@ -1812,6 +2058,23 @@ __global__ __launch_bounds__(kThreads, 2) void train_dkv_mfma_kernel(TrainParams
   if constexpr (PART != 1) emit(std::integral_constant<int, 2>{});
 }
 
+// Whether fp32 attention of n tokens runs on the vector ALUs: short sequences,
+// where the tiles' 32 rows are mostly padding, the more so the more tiles there are
+// (their LDS lets two workgroups run on a compute unit at d = 128, four at 64).
+// Forward and backward, time on tiles over time on the vector ALUs: d = 128, 256 units of
+// 4 tokens 1.6 (one query head) to 1.04 (eight), of 8 1.24 to 0.90, of 12 1.15 to 0.81; 512 units of
+// 20 1.17 to 1.04, of 28 0.98 to 0.88, of 33 1.22 to 0.96; 1024 units of 28 1.29 to 1.05, of 32 1.11 to
+// 0.77, of 40 1.24 to 0.92; d = 64, 256 units of 2 1.20 to 1.06, of 6 0.99 to 0.82; 1024 units of 8 1.68 to
+// 1.10, of 20 1.08 to 0.82, of 32 0.75 to 0.47.
+bool train_f32_short(int head_dim, int group, int64_t units, int64_t n) {
+  if (head_dim == 64)
+    return n <= 2 || (n <= 4 && group <= 4) || (n <= 24 && units >= 512 && n * (30 + 12 * group) <= units);
+  if (n <= 4 || (n <= 6 && group <= 4) || (n <= 12 && n * group <= 16)) return true;
+  if (units < 448) return false;
+  if (n <= 24 || (n > 32 && n <= 36) || (n <= 28 && units > 640)) return true;
+  return group == 1 ? units >= 640 && n <= 48 : units >= 1024 && n <= 40 && n != 32;
+}
+
 int blocks_for(int64_t threads) {
   return static_cast<int>((threads + kThreads - 1) / kThreads);
 }
@@ -1840,9 +2103,15 @@ hipError_t train_forward_impl(const TrainParams &p, hipStream_t s) {
                        dim3(kThreads), 0, s, p, ntiles);
   } else {
     hipLaunchKernelGGL((train_states_kernel<ES, D>), dim3((p.n + 7) / 8, U), dim3(64), 0, s, p);
-    const int ntiles = (p.n + 32 / G - 1) / (32 / G);
-    hipLaunchKernelGGL((train_fwd_f32_kernel<D, G>), dim3(unsigned(U) * ntiles), dim3(kThreads), 0, s, p,
-                       ntiles);
+    if (train_f32_short(D, G, U, p.n)) {
+      const int ngroups = (p.n + Rows<G>::TG - 1) / Rows<G>::TG;
+      hipLaunchKernelGGL((train_fwd_kernel<ES, D, G>), dim3(blocks_for(int64_t(U) * ngroups * 64)),
+                         dim3(kThreads), 0, s, p, ngroups);
+    } else {
+      const int ntiles = (p.n + 32 / G - 1) / (32 / G);
+      hipLaunchKernelGGL((train_fwd_f32_kernel<D, G>), dim3(unsigned(U) * ntiles), dim3(kThreads), 0, s, p,
+                         ntiles);
+    }
   }
   return hipGetLastError();
 }
@@ -1861,15 +2130,24 @@ hipError_t train_backward_impl(const TrainParams &p, hipStream_t s) {
     hipLaunchKernelGGL((train_dkv_mfma_kernel<D, G, 2>), dim3(8 * ((U + 7) / 8) * stiles),
                        dim3(kThreads), 0, s, p, stiles);
   } else {
-    const int ntiles = (p.n + 32 / G - 1) / (32 / G), stiles = (p.n + 31) / 32;
-    hipLaunchKernelGGL((train_dq_f32_kernel<D, G>), dim3(unsigned(U) * ntiles), dim3(kThreads), 0, s, p,
-                       ntiles);
-    const dim3 sgrid(unsigned(U) * stiles);
-    if constexpr (D == 64) {
-      hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 0>), sgrid, dim3(kThreads), 0, s, p, stiles);
+    if (train_f32_short(D, G, U, p.n)) {
+      const int ngroups = (p.n + Rows<G>::TG - 1) / Rows<G>::TG;
+      hipLaunchKernelGGL((train_dq_kernel<ES, D, G>), dim3(blocks_for(int64_t(U) * ngroups * 64)),
+                         dim3(kThreads), 0, s, p, ngroups);
+      const int nblocks = (p.n + 3) / 4;
+      hipLaunchKernelGGL((train_dkv_kernel<ES, D, G>), dim3(blocks_for(int64_t(U) * nblocks * 64)),
+                         dim3(kThreads), 0, s, p, nblocks);
     } else {
-      hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 1>), sgrid, dim3(kThreads), 0, s, p, stiles);
-      hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 2>), sgrid, dim3(kThreads), 0, s, p, stiles);
+      const int ntiles = (p.n + 32 / G - 1) / (32 / G), stiles = (p.n + 31) / 32;
+      hipLaunchKernelGGL((train_dq_f32_kernel<D, G>), dim3(unsigned(U) * ntiles), dim3(kThreads), 0, s, p,
+                         ntiles);
+      const dim3 sgrid(unsigned(U) * stiles);
+      if constexpr (D == 64) {
+        hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 0>), sgrid, dim3(kThreads), 0, s, p, stiles);
+      } else {
+        hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 1>), sgrid, dim3(kThreads), 0, s, p, stiles);
+        hipLaunchKernelGGL((train_dkv_f32_kernel<D, G, 2>), sgrid, dim3(kThreads), 0, s, p, stiles);
+      }
     }
   }
   if constexpr (ES == 2) {
