@@ -1584,7 +1584,17 @@ __global__ __launch_bounds__(kThreads) void prefill_decide_kernel(PrefillParams 
       k0[j] = neuron(kb, kst, koff, tw);
       q0[j] = STAGE && p.omega_src == 0 ? neuron(qb, qst, qoff, tw) : 0.0f;
     }
-    if (STAGE && p.omega_src == 1) {   // the group's sum, a batch of loads in flight per head
+    if (STAGE && p.omega_src == 1 && p.n - t00 <= kThreads) {
+      // the group's sum, one token per thread: every head's load in flight (1024 units of 9
+      // tokens, 8 heads: 34 us a call head after head, this way 19)
+      float x[8];
+#pragma unroll
+      for (int h = 0; h < 8; ++h)
+        x[h] = h < G ? neuron(qb + h * p.qs[2] * ES, qst, qoff, t00 + wave * 64) : 0.0f;
+#pragma unroll
+      for (int h = 0; h < 8; ++h)
+        if (h < G) q0[0] += sigmoid_floor(x[h]);
+    } else if (STAGE && p.omega_src == 1) {   // a batch of loads in flight per head
       for (int h = 0; h < G; ++h) {
         float x[kBatch];
 #pragma unroll
