@@ -186,7 +186,8 @@ dmc_status dmc_prefill_compress(dmc_cache *cache, int32_t layer,
  *     tokens t >= prompt_lens[b] are written as zeros.  out must not overlap
  *     q, k or v.
  * Runs on the matrix cores (bf16: v_mfma_f32_32x32x16_bf16, fp32:
- * v_mfma_f32_32x32x2_f32; fp32 accumulation).  Uses the staging area sized by
+ * v_mfma_f32_32x32x2_f32; fp32 accumulation), fp32 prompts of few tokens on the
+ * vector ALUs.  Uses the staging area sized by
  * max_prompt_len, including the per-32-token running-sum records. */
 dmc_status dmc_prefill_attend(dmc_cache *cache, int32_t layer,
                               const void *k_dev, const int64_t k_strides[3],

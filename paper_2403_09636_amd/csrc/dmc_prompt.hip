@@ -8,7 +8,7 @@
 // closed before it -- slots 0 .. seg(i)-1 of the compacted cache -- and the
 // running (partial) mean of its own segment up to and including token i.
 //
-// Both kernels (bf16, fp32) run after the compaction passes, which leave in the
+// The kernels (bf16, fp32, fp32 prompts of few tokens) run after the compaction passes, which leave in the
 // workspace the decisions and importance scores of every prompt token, the
 // per-64-token segment-start counts, the finished cache and, for every
 // 32-token boundary that falls inside a segment, the segment's running sums

@@ -19,7 +19,8 @@
 // and the decision / importance neurons get theirs through alpha and omega.
 //
 // Attention runs on the matrix cores in both dtypes (v_mfma_f32_32x32x16_bf16,
-// v_mfma_f32_32x32x2_f32): forward, dq, and the states' gradients.  The states
+// v_mfma_f32_32x32x2_f32): forward, dq, and the states' gradients; short fp32
+// sequences use the vector ALUs.  The states
 // and token passes are matrix products for bf16 and vector-ALU kernels (lanes
 // own head-dim elements) for fp32.
 #include <type_traits>
